@@ -590,27 +590,6 @@ __device__ __forceinline__ void em_visit(const EmCtx &c, float4 r, Accum &a) {
   }
 }
 
-// Pick m of a pixel: the 16-bit field m of the stream-1 Philox words gives a
-// code c uniform over (48 neighbours) x spp; returns the LDS index of that
-// candidate.  All products fit 24 bits (full-rate v_mul_u32_u24); the code is
-// split as c = o spp + s by (c ceil(2^16/spp)) >> 16, exact for c < 48 spp,
-// and the neighbour o (centre skipped) of the 7x7 window sits at row o / 7 =
-// (37 o) >> 8 (exact for o < 49), column o mod 7.
-template <int SA, int SW>
-__device__ __forceinline__ int pick_entry(uint4 w4, int m, uint32_t cs, uint32_t inv_spp, uint32_t spp,
-                                          int own) {
-  const int wsel = (m >> 1) & 3;
-  const uint32_t word = wsel == 0 ? w4.x : wsel == 1 ? w4.y : wsel == 2 ? w4.z : w4.w;
-  const uint32_t h = (m & 1) ? (word >> 16) : (word & 0xFFFFu);
-  const uint32_t c = __umul24(h, cs) >> 16;
-  const uint32_t o0 = __umul24(c, inv_spp) >> 16;
-  const uint32_t s = c - __umul24(o0, spp);
-  const uint32_t o = o0 + (o0 >= (uint32_t)(kCand / 2) ? 1u : 0u);
-  const uint32_t row = __umul24(o, 37u) >> 8;
-  return (int)__umul24(s, (uint32_t)SA) + own + (int)(o + __umul24(row, (uint32_t)(SW - kSide))) -
-         (kR * SW + kR);
-}
-
 // Bytes of the pick table in dynamic LDS (after the records and the lists).
 __host__ __device__ constexpr int pick_table_bytes(int spp) { return (kCand * spp * 2 + 15) & ~15; }
 
@@ -618,7 +597,7 @@ __host__ __device__ constexpr int pick_table_bytes(int spp) { return (kCand * sp
 // its candidate's staged record from the pixel's own: s SA + dy SW + dx with
 // (o, s) = (c div spp, c mod spp), the centre of the window skipped, and
 // (dx, dy) = (o mod 7 - 3, o div 7 - 3).  Built once per block, so that a
-// pick costs one LDS read instead of the integer arithmetic of pick_entry.
+// pick costs one LDS read instead of integer arithmetic.
 template <int SA, int SW>
 __device__ __forceinline__ void build_pick_table(int16_t *tab, int spp) {
   // c div spp = (c ceil(2^16 / spp)) >> 16, exact for c < 48 spp
@@ -806,6 +785,7 @@ __device__ __forceinline__ bool stale_history(const ParamsK &P, const Pixel &px,
 // block on entry.  Each thread offers `item`; returns the item this lane
 // takes.
 constexpr int kMaxLen = kMaxSpp + 21;
+constexpr int kTrained = 128;  // flag beside a list length: the pixel trains
 
 template <int NT>
 __device__ __forceinline__ int balance(int len, int item, int *cnt, uint16_t *perm, int rot) {
@@ -865,8 +845,8 @@ struct EmInput {
 };
 
 // Issue the loads of a tile's inputs (no use of the results here).
-template <typename TG, int TW, int TH>
-__device__ __forceinline__ void em_load(const ViewK &v, const SamplesK &S, const TG *gamma, int tx0, int ty0,
+template <typename Op, int TW, int TH>
+__device__ __forceinline__ void em_load(const ViewK &v, const SamplesK &S, const Op &op, int tx0, int ty0,
                                         EmInput<TW, TH> &R) {
   using In = EmInput<TW, TH>;
   const int plane = v.H * v.pitch;
@@ -876,7 +856,7 @@ __device__ __forceinline__ void em_load(const ViewK &v, const SamplesK &S, const
   R.n = R.o = V3{0, 0, 0};
   if (x0 < v.W && y0 < v.H) {
     const int idx0 = row_off(y0, v.pitch) + x0;
-    R.k = gamma_get(&at(gamma + 7 * plane, idx0), 7);
+    R.k = op.epoch(plane, idx0);
     R.rough = at(v.rough, idx0);
     R.n = load3(v.n, plane, idx0);
     R.o = load3(v.o, plane, idx0);
@@ -903,6 +883,82 @@ __device__ __forceinline__ void em_load(const ViewK &v, const SamplesK &S, const
   }
 }
 
+// What a training tile does with each pixel's training set, as a type `Op`:
+//   epoch(plane, idx)        the k that decides the number of picks
+//   load(plane, idx, g)      the pixel's state or parameters
+//   Ctx context(P, px, g)    what a visit needs of the pixel
+//   visit(ctx, record, acc)  one member of the training set
+//   finish(P, ctx, acc, idx, g)  the pixel's results, in g
+//   put(ch), store(plane, idx, out)  the channels of g that are results
+// kEvery: the pixels with an empty training set have results of their own
+// (EM leaves them as they are).  EmOp is the EM update of a state.
+template <typename TG>
+struct EmOp {
+  using Ctx = EmCtx;
+  using Acc = Accum;
+  static constexpr bool kEvery = false;
+  TG *gamma;
+  __device__ __forceinline__ float epoch(int plane, int idx) const { return gamma_get(&at(gamma + 7 * plane, idx), 7); }
+  __device__ __forceinline__ void load(int plane, int idx, float g[8]) const { gamma_load(gamma, plane, idx, g); }
+  static __device__ __forceinline__ Ctx context(const ParamsK &P, const Pixel &px, const float g[8]) {
+    return Ctx{px, lobe_term(gauss_setup(g[0], g[1], g[2], g[3], g[4], P.eps), g[5]), g[5]};
+  }
+  static __device__ __forceinline__ void visit(const Ctx &c, float4 r, Acc &a) { em_visit(c, r, a); }
+  __device__ __forceinline__ void finish(const ParamsK &P, const Ctx &c, Acc &a, int, float g[8]) const {
+    if (!(a.B0 > 0.0f)) return;  // no weight: the model stays as it is
+    accum_to_unit(a, c.T);
+    em_merge_online(P, g, a);
+  }
+  static constexpr bool put(int ch) { return ch < 8; }
+  __device__ __forceinline__ void store(int plane, int idx, const float out[8]) const {
+    gamma_store(gamma, plane, idx, out);
+  }
+};
+
+// Plain batch EM of one pixel: `iterations` rounds on its training list (mu,
+// Sigma and pi replaced; W and k kept).
+__device__ __forceinline__ void em_batch(const ParamsK &P, const Pixel &px, const float4 *lds, const uint16_t *list,
+                                         int me, int len, int nt, int iterations, float g[8]) {
+  for (int it = 0; it < iterations; ++it) {
+    const EmCtx c = EmOp<float>::context(P, px, g);
+    Accum a = {0, 0, 0, 0, 0, 0, 0};
+    // more state live than online: one record at a time
+    for_each_record<0>(lds, list, nt, me, 0, 1, len, [&](float4 r) { em_visit(c, r, a); });
+    if (!(a.B0 > 0.0f)) break;
+    accum_to_unit(a, c.T);
+    if (a.B1 > 0.0f) {
+      g[0] = a.mx;
+      g[1] = a.my;
+      g[2] = a.sxx;
+      g[3] = a.sxy;
+      g[4] = a.syy;
+    }
+    float pn = div_pos(a.B1, a.B0);
+    if (!(P.flags & kNoClamp)) pn = fminf(fmaxf(pn, P.pi_lo), P.pi_hi);
+    g[5] = pn;
+  }
+}
+
+// A tile's results from the sorted lanes to global memory in natural order
+// (full cache lines), through LDS [channels][NT] over the dead records.
+template <typename Op, int NT>
+__device__ __forceinline__ void tile_write_back(const Op &op, float *wb, int me, bool me_in, const float g[8], int t,
+                                                bool in_image, int plane, int idx0) {
+  if (me_in) {
+#pragma unroll
+    for (int ch = 0; ch < 8; ++ch)
+      if (Op::put(ch)) wb[ch * NT + me] = g[ch];
+  }
+  __syncthreads();
+  if (in_image) {
+    float go[8];
+#pragma unroll
+    for (int ch = 0; ch < 8; ++ch)
+      if (Op::put(ch)) go[ch] = wb[ch * NT + t];
+    op.store(plane, idx0, go);
+  }
+}
+
 // One training tile.  Its inputs arrive in R (what decides each pixel's
 // candidate count, natural order; records of plane 0; further planes are
 // staged here): stage the records in LDS; sort the pixels by candidate count
@@ -915,8 +971,8 @@ __device__ __forceinline__ void em_load(const ViewK &v, const SamplesK &S, const
 // Dynamic LDS: records [spp][SH][SW] float4, then lists [spp + 20][NT]
 // uint16, then the pick table [48 spp] int16; the write-back reuses the area
 // ([8][NT] float).
-template <typename TG, int TW, int TH, bool STALE = false, bool BATCH = false>
-__device__ __forceinline__ void em_tile(const ParamsK &P, const ViewK &v, const SamplesK &S, TG *gamma,
+template <typename Op, int TW, int TH, bool STALE = false, bool BATCH = false>
+__device__ __forceinline__ void em_tile(const ParamsK &P, const ViewK &v, const SamplesK &S, const Op &op,
                                         int iterations, int tx0, int ty0, int rot, float4 *lds,
                                         EmShared<TW * TH> &sh, const EmInput<TW, TH> &R) {
   constexpr int SW = TW + 2 * kR, SH = TH + 2 * kR, SA = SW * SH, NT = TW * TH, IT = EmInput<TW, TH>::IT;
@@ -957,68 +1013,44 @@ __device__ __forceinline__ void em_tile(const ParamsK &P, const ViewK &v, const 
       len = build_list<TW, TH>(P, lds, ptab, list, pa, lx, ly, nc - S.spp, S.spp,
                                (uint32_t)(row_off(ty0 + ly, v.W) + tx0 + lx));
     }
-    sh.work[pa] = (uint8_t)len;
+    sh.work[pa] = (uint8_t)(Op::kEvery && nc > 0 ? len | kTrained : len);
     // E- and M-steps: pixels by decreasing list length
     me = balance<NT>(len, pa, sh.cnt[1], sh.perm, rot + 1);
   }
-  const int len = sh.work[me];
-  EmCtx c;
-  float g[8];
+  const int len = Op::kEvery ? sh.work[me] & (kTrained - 1) : sh.work[me];
+  const bool run = Op::kEvery ? (sh.work[me] & kTrained) != 0 : len > 0;
+  float g[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   // every pixel of the tile, trained or not, passes its state to the
   // natural-order write-back through LDS (the loads run for the trained
   // lanes of the wave anyway)
   const int mex = tx0 + me % TW, mey = ty0 + me / TW;
   const bool me_in = mex < v.W && mey < v.H;
   const int idx = row_off(mey, v.pitch) + mex;
-  if (me_in) gamma_load(gamma, plane, idx, g);
-  if (len > 0) {
-    c.px = make_pixel(P, load3(v.n, plane, idx), load3(v.o, plane, idx), at(v.rough, idx), at(v.alb, idx));
-    if (STALE && !BATCH && g[7] >= 1.0f && stale_history(P, c.px, g, lds, list, me, len, NT)) gamma_reset(P, g);
+  if (Op::kEvery ? run : me_in) op.load(plane, idx, g);
+  Pixel px;
+  if (run) {
+    px = make_pixel(P, load3(v.n, plane, idx), load3(v.o, plane, idx), at(v.rough, idx), at(v.alb, idx));
+    if constexpr (STALE && !BATCH)
+      if (g[7] >= 1.0f && stale_history(P, px, g, lds, list, me, len, NT)) gamma_reset(P, g);
   }
-  if (len > 0) {  // otherwise no training sample (or no pixel): the model stays as it is
-    const int iters = BATCH ? iterations : 1;
-    for (int it = 0; it < iters; ++it) {
-      c.T = lobe_term(gauss_setup(g[0], g[1], g[2], g[3], g[4], P.eps), g[5]);
-      c.pi = g[5];
-      Accum a = {0, 0, 0, 0, 0, 0, 0};
+  if (run) {
+    if constexpr (BATCH) {
+      em_batch(P, px, lds, list, me, len, NT, iterations, g);
+    } else {
+      const typename Op::Ctx c = Op::context(P, px, g);
+      typename Op::Acc a = {};
       // at spp 1 one record at a time: 8 waves per SIMD cover the LDS
       // latency, and a look-ahead's index arithmetic measured 3% slower;
       // above, the staged records leave 4-5 waves and the reads go ahead
-      // (batch EM, with more state live, keeps one record at a time)
-      if (!BATCH && S.spp > 1)
-        for_each_record<2>(lds, list, NT, me, 0, 1, len, [&](float4 r) { em_visit(c, r, a); });
+      if (S.spp > 1)
+        for_each_record<2>(lds, list, NT, me, 0, 1, len, [&](float4 r) { Op::visit(c, r, a); });
       else
-        for_each_record<0>(lds, list, NT, me, 0, 1, len, [&](float4 r) { em_visit(c, r, a); });
-      if (!(a.B0 > 0.0f)) break;
-      accum_to_unit(a, c.T);
-      if (!BATCH) {
-        em_merge_online(P, g, a);
-      } else {
-        if (a.B1 > 0.0f) {
-          g[0] = a.mx;
-          g[1] = a.my;
-          g[2] = a.sxx;
-          g[3] = a.sxy;
-          g[4] = a.syy;
-        }
-        float pn = div_pos(a.B1, a.B0);
-        if (!(P.flags & kNoClamp)) pn = fminf(fmaxf(pn, P.pi_lo), P.pi_hi);
-        g[5] = pn;
-      }
+        for_each_record<0>(lds, list, NT, me, 0, 1, len, [&](float4 r) { Op::visit(c, r, a); });
+      op.finish(P, c, a, idx, g);
     }
   }
   __syncthreads();  // records and lists are no longer read
-  if (me_in) {
-#pragma unroll
-    for (int ch = 0; ch < 8; ++ch) wb[ch * NT + me] = g[ch];
-  }
-  __syncthreads();
-  if (in_image) {
-    float go[8];
-#pragma unroll
-    for (int ch = 0; ch < 8; ++ch) go[ch] = wb[ch * NT + t];
-    gamma_store(gamma, plane, row_off(y0, v.pitch) + x0, go);
-  }
+  tile_write_back<Op, NT>(op, wb, me, me_in, g, t, in_image, plane, row_off(y0, v.pitch) + x0);
 }
 
 // Two-pass training tile (online EM from spp 4).  Above spp 1 the staged
@@ -1144,8 +1176,8 @@ __device__ __forceinline__ int build_list2(const ParamsK &P, const uint32_t *vb,
   return a + b;
 }
 
-template <typename TG, int TW, int TH>
-__device__ __forceinline__ void em_tile2(const ParamsK &P, const ViewK &v, const SamplesK &S, TG *gamma, int tx0,
+template <typename Op, int TW, int TH>
+__device__ __forceinline__ void em_tile2(const ParamsK &P, const ViewK &v, const SamplesK &S, const Op &op, int tx0,
                                          int ty0, int rot, float4 *lds, EmShared<TW * TH> &sh,
                                          const EmInput<TW, TH> &R) {
   constexpr int SW = TW + 2 * kR, SH = TH + 2 * kR, SA = SW * SH, NT = TW * TH, IT = EmInput<TW, TH>::IT;
@@ -1190,55 +1222,39 @@ __device__ __forceinline__ void em_tile2(const ParamsK &P, const ViewK &v, const
       len = build_list2<TW, TH>(P, vb, ptab, list, pa, lx, ly, nc - spp, spp,
                                 (uint32_t)(row_off(ty0 + ly, v.W) + tx0 + lx), n0);
     }
-    sh.work[pa] = (uint8_t)len;
+    sh.work[pa] = (uint8_t)(Op::kEvery && nc > 0 ? len | kTrained : len);
     work0[pa] = (uint8_t)n0;
     // each pass lasts as long as its longest list in the wave, so the lanes
     // are grouped by the longer of their two parts (max(n0) + max(n1) per
     // wave), not by the whole list
     me = balance<NT>(max(n0, len - n0), pa, sh.cnt[1], sh.perm, rot + 1);
   }
-  const int len = sh.work[me], n0 = work0[me];
-  float g[8];
+  const int len = Op::kEvery ? sh.work[me] & (kTrained - 1) : sh.work[me], n0 = work0[me];
+  const bool run = Op::kEvery ? (sh.work[me] & kTrained) != 0 : len > 0;
+  float g[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   const int mex = tx0 + me % TW, mey = ty0 + me / TW;
   const bool me_in = mex < v.W && mey < v.H;
   const int idx = row_off(mey, v.pitch) + mex;
-  if (me_in) gamma_load(gamma, plane, idx, g);
-  Accum a = {0, 0, 0, 0, 0, 0, 0};
+  if (Op::kEvery ? run : me_in) op.load(plane, idx, g);
+  typename Op::Acc a = {};
   // the pixel's context is built for each pass (its loads hit the caches):
   // across the restaging only the sums and the state stay in registers
-  if (len > 0) {
-    EmCtx c;
-    c.px = make_pixel(P, load3(v.n, plane, idx), load3(v.o, plane, idx), at(v.rough, idx), at(v.alb, idx));
-    c.T = lobe_term(gauss_setup(g[0], g[1], g[2], g[3], g[4], P.eps), g[5]);
-    c.pi = g[5];
-    for_each_record<2>(rec, list, NT, me, 0, 1, n0, [&](float4 r) { em_visit(c, r, a); });
+  if (run) {
+    const typename Op::Ctx c = Op::context(
+        P, make_pixel(P, load3(v.n, plane, idx), load3(v.o, plane, idx), at(v.rough, idx), at(v.alb, idx)), g);
+    for_each_record<2>(rec, list, NT, me, 0, 1, n0, [&](float4 r) { Op::visit(c, r, a); });
   }
   __syncthreads();  // the first planes' records are no longer read
   stage2<TW, TH>(v, S, rec, vb, tx0, ty0, pg, spp, 0, false);
   __syncthreads();
-  if (len > 0) {
-    EmCtx c;
-    c.px = make_pixel(P, load3(v.n, plane, idx), load3(v.o, plane, idx), at(v.rough, idx), at(v.alb, idx));
-    c.T = lobe_term(gauss_setup(g[0], g[1], g[2], g[3], g[4], P.eps), g[5]);
-    c.pi = g[5];
-    for_each_record<2>(rec, list, NT, me, cap - 1, -1, len - n0, [&](float4 r) { em_visit(c, r, a); });
-    if (a.B0 > 0.0f) {  // otherwise no weight: the model stays as it is
-      accum_to_unit(a, c.T);
-      em_merge_online(P, g, a);
-    }
+  if (run) {
+    const typename Op::Ctx c = Op::context(
+        P, make_pixel(P, load3(v.n, plane, idx), load3(v.o, plane, idx), at(v.rough, idx), at(v.alb, idx)), g);
+    for_each_record<2>(rec, list, NT, me, cap - 1, -1, len - n0, [&](float4 r) { Op::visit(c, r, a); });
+    op.finish(P, c, a, idx, g);
   }
   __syncthreads();  // records and lists are no longer read
-  if (me_in) {
-#pragma unroll
-    for (int ch = 0; ch < 8; ++ch) wb[ch * NT + me] = g[ch];
-  }
-  __syncthreads();
-  if (in_image) {
-    float go[8];
-#pragma unroll
-    for (int ch = 0; ch < 8; ++ch) go[ch] = wb[ch * NT + t];
-    gamma_store(gamma, plane, row_off(y0, v.pitch) + x0, go);
-  }
+  tile_write_back<Op, NT>(op, wb, me, me_in, g, t, in_image, plane, row_off(y0, v.pitch) + x0);
 }
 
 // One tile per block (blocks are mapped to XCD bands by xcd_tile); with the
@@ -1254,114 +1270,129 @@ __global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(TWO ? 5 
   const int tile = xcd_tile(blockIdx.x, n_tiles);
   const int tx0 = (tile % tiles_x) * TW, ty0 = (tile / tiles_x) * TH;
   build_em_pick_table<TW, TH, TWO>(lds, S.spp);  // before the loads: fewer live registers
+  const EmOp<TG> op{gamma};
   EmInput<TW, TH> R;
-  em_load(v, S, gamma, tx0, ty0, R);
-  if (TWO)
-    em_tile2<TG, TW, TH>(P, v, S, gamma, tx0, ty0, (int)blockIdx.x, lds, sh, R);
+  em_load(v, S, op, tx0, ty0, R);
+  if constexpr (TWO)
+    em_tile2(P, v, S, op, tx0, ty0, (int)blockIdx.x, lds, sh, R);
   else
-    em_tile<TG, TW, TH, STALE, BATCH>(P, v, S, gamma, iterations, tx0, ty0, (int)blockIdx.x, lds, sh, R);
+    em_tile<EmOp<TG>, TW, TH, STALE, BATCH>(P, v, S, op, iterations, tx0, ty0, (int)blockIdx.x, lds, sh, R);
 }
 
 // ---------------------------------------------------------------------------
 // Weighted NLL of the mixture over the training set and its adjoint.
 struct NllAccum {
-  float loss, gmx, gmy, gxx, gxy, gyy, gl;
+  float loss, gmx, gmy, gxx, gxy, gyy, gl;  // loss in units of ln 2
 };
 
 struct NllCtx {
   Pixel px;
-  Gauss G;
-  float pi, one_m_pi, mux, muy, ia, ib, ic;
+  LobeTerm T;
+  float pi, one_m_pi, ia, ib, ic;  // ia, ib, ic: the inverse of Sigma + eps I
 };
 
-__device__ __forceinline__ void nll_visit(const NllCtx &c, float4 r, NllAccum &a) {
-  if (r.w == 0.0f) return;
-  const V3 l = to_local(c.px.f, V3{r.x, r.y, r.z});
-  if (l.z <= 0.0f) return;
-  float ux, uy, f, pb;
-  hemi2sq(l, ux, uy);
-  brdf_eval(c.px, l, f, pb);
-  const float w = r.w * f * l.z;
-  const float pg = gauss_pdf_acc(c.G, ux, uy);
-  const float ga = c.pi * pg;
-  const float D = fmaf(c.one_m_pi, pb, ga);
-  a.loss = fmaf(-w, logf(D), a.loss);
-  const float gam = D > 0.0f ? ga / D : 0.0f;
-  const float dx = ux - c.mux, dy = uy - c.muy;
-  const float vx = fmaf(c.ia, dx, c.ib * dy), vy = fmaf(c.ib, dx, c.ic * dy);
-  const float wg = w * gam;
-  a.gmx = fmaf(-wg, vx, a.gmx);
-  a.gmy = fmaf(-wg, vy, a.gmy);
-  a.gxx = fmaf(-0.5f * wg, fmaf(vx, vx, -c.ia), a.gxx);
-  a.gxy = fmaf(-0.5f * wg, fmaf(vx, vy, -c.ib), a.gxy);
-  a.gyy = fmaf(-0.5f * wg, fmaf(vy, vy, -c.ic), a.gyy);
-  a.gl = fmaf(-w, gam - c.pi, a.gl);
-}
+// NLL (LOSS) and its gradient (GRAD) of the pixels' parameters theta = (mu,
+// Cholesky factor, logit pi, -, k).  The training tile of the EM update runs
+// it: the picks of a pixel are examined once against the staged records and
+// only the kept ones visited, by lanes sorted to nearly equal lists.  (One
+// lane per pixel in image order visited all of its candidates: 24 visits a
+// wave at spp 4, where the sorted lists need about 11.)
+template <bool LOSS, bool GRAD>
+struct NllOp {
+  using Ctx = NllCtx;
+  using Acc = NllAccum;
+  static constexpr bool kEvery = true;
+  const float *theta, *grad_out;
+  float *grad, *nll;
+  __device__ __forceinline__ float epoch(int plane, int idx) const { return at(theta + 7 * plane, idx); }
+  __device__ __forceinline__ void load(int plane, int idx, float g[8]) const {
+#pragma unroll
+    for (int ch = 0; ch < 6; ++ch) g[ch] = at(theta + ch * plane, idx);
+  }
+  static __device__ __forceinline__ Ctx context(const ParamsK &P, const Pixel &px, const float g[8]) {
+    Ctx c;
+    const float l11 = g[2], l21 = g[3], l22 = g[4];
+    const Gauss G = gauss_setup(g[0], g[1], l11 * l11, l11 * l21, fmaf(l21, l21, l22 * l22), P.eps);
+    c.px = px;
+    c.pi = 1.0f / (1.0f + expf(-g[5]));
+    c.one_m_pi = 1.0f - c.pi;
+    c.T = lobe_term(G, c.pi);
+    // (L L^T)^-1 from the whitening z = L^-1 r, z1 = i11 rx, z2 = i22 ry + c21 z1
+    const float b = c.T.c21 * G.i11;
+    c.ia = fmaf(b, b, G.i11 * G.i11);
+    c.ib = b * G.i22;
+    c.ic = G.i22 * G.i22;
+    return c;
+  }
+  static __device__ __forceinline__ void visit(const Ctx &c, float4 r, Acc &a) {
+    if (r.w == 0.0f) return;
+    const V3 l = to_local(c.px.f, V3{r.x, r.y, r.z});
+    if (l.z <= 0.0f) return;
+    float ox, oy, f, pb;
+    hemi2sq_c(l, ox, oy);
+    const float rx = fmaf(0.5f, ox, c.T.hx), ry = fmaf(0.5f, oy, c.T.hy);
+    brdf_eval(c.px, l, f, pb);
+    const float w = r.w * f * l.z;
+    const float z1 = rx * c.T.i11;
+    const float z2 = fmaf(ry, c.T.i22, z1 * c.T.c21);
+    float ga = c.T.pi_norm * __builtin_amdgcn_exp2f(-0.72134752044448170368f * fmaf(z1, z1, z2 * z2));
+    float D = fmaf(c.one_m_pi, pb, ga), off = 0.0f;
+    if (D < 0x1p-100f) {  // the hardware logarithm and reciprocal take subnormals for zero
+      ga *= 0x1p64f;
+      D *= 0x1p64f;
+      off = 64.0f;
+    }
+    if (LOSS) a.loss = fmaf(w, off - __builtin_amdgcn_logf(D), a.loss);
+    if (GRAD) {
+      const float gam = D > 0.0f ? ga * __builtin_amdgcn_rcpf(D) : 0.0f;
+      // Sigma^-1 r = L^-T z
+      const float vx = c.T.i11 * fmaf(c.T.c21, z2, z1), vy = c.T.i22 * z2;
+      const float wg = w * gam, hg = -0.5f * wg;
+      a.gmx = fmaf(-wg, vx, a.gmx);
+      a.gmy = fmaf(-wg, vy, a.gmy);
+      a.gxx = fmaf(hg, fmaf(vx, vx, -c.ia), a.gxx);
+      a.gxy = fmaf(hg, fmaf(vx, vy, -c.ib), a.gxy);
+      a.gyy = fmaf(hg, fmaf(vy, vy, -c.ic), a.gyy);
+      a.gl = fmaf(-w, gam - c.pi, a.gl);
+    }
+  }
+  __device__ __forceinline__ void finish(const ParamsK &, const Ctx &, const Acc &a, int idx, float g[8]) const {
+    if (GRAD) {
+      const float sc = grad_out ? at(grad_out, idx) : 1.0f;
+      const float l11 = g[2], l21 = g[3], l22 = g[4];
+      g[0] = sc * a.gmx;
+      g[1] = sc * a.gmy;
+      g[2] = sc * 2.0f * fmaf(a.gxx, l11, a.gxy * l21);
+      g[3] = sc * 2.0f * fmaf(a.gxy, l11, a.gyy * l21);
+      g[4] = sc * 2.0f * (a.gyy * l22);
+      g[5] = sc * a.gl;
+    }
+    if (LOSS) g[6] = a.loss * 0.693147180559945309417f;
+  }
+  static constexpr bool put(int ch) { return (GRAD && ch < 6) || (LOSS && ch == 6); }
+  __device__ __forceinline__ void store(int plane, int idx, const float out[8]) const {
+    if (GRAD) {
+#pragma unroll
+      for (int ch = 0; ch < 8; ++ch) at(grad + ch * plane, idx) = ch < 6 ? out[ch] : 0.0f;
+    }
+    if (LOSS) at(nll, idx) = out[6];
+  }
+};
 
-template <int TW, int TH>
-__global__ __launch_bounds__(TW *TH) void k_nll(ParamsK P, ViewK v, SamplesK S, const float *__restrict__ theta,
-                                                const float *__restrict__ grad_out, float *__restrict__ grad,
-                                                float *__restrict__ nll, int tiles_x, int n_tiles) {
-  extern __shared__ float4 lds[];
-  constexpr int SW = TW + 2 * kR, SH = TH + 2 * kR, SA = SW * SH;
+template <int TW, int TH, bool LOSS, bool GRAD, bool TWO>
+__global__ __launch_bounds__(TW *TH) void k_nll(ParamsK P, ViewK v, SamplesK S, NllOp<LOSS, GRAD> op, int tiles_x,
+                                                int n_tiles) {
+  extern __shared__ float4 lds[];  // records, lists and the pick table (em_lds_front, em2_lds_front)
+  __shared__ EmShared<TW * TH> sh;
   const int tile = xcd_tile(blockIdx.x, n_tiles);
   const int tx0 = (tile % tiles_x) * TW, ty0 = (tile / tiles_x) * TH;
-  stage_records<TW, TH>(v, S, lds, tx0, ty0);
-  __syncthreads();
-  const int lx = threadIdx.x % TW, ly = threadIdx.x / TW;
-  const int x = tx0 + lx, y = ty0 + ly;
-  if (x >= v.W || y >= v.H) return;
-  const int plane = v.H * v.pitch;
-  const int idx = y * v.pitch + x;
-  const V3 n = load3(v.n, plane, idx);
-  const V3 o = load3(v.o, plane, idx);
-  const float rough = v.rough[idx];
-  float th[8];
-#pragma unroll
-  for (int ch = 0; ch < 8; ++ch) th[ch] = theta[ch * plane + idx];
-  NllAccum a = {0, 0, 0, 0, 0, 0, 0};
-  float gr[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  if (dot3(n, o) > 0.0f && rough >= P.rough_min) {
-    NllCtx c;
-    c.px = make_pixel(P, n, o, rough, v.alb[idx]);
-    const float l11 = th[2], l21 = th[3], l22 = th[4];
-    const float sxx = l11 * l11, sxy = l11 * l21, syy = fmaf(l21, l21, l22 * l22);
-    c.G = gauss_setup(th[0], th[1], sxx, sxy, syy, P.eps);
-    c.pi = 1.0f / (1.0f + expf(-th[5]));
-    c.one_m_pi = 1.0f - c.pi;
-    c.mux = th[0];
-    c.muy = th[1];
-    const float A = sxx + P.eps, B = sxy, Cc = syy + P.eps;
-    const float idet = 1.0f / fmaf(A, Cc, -B * B);
-    c.ia = Cc * idet;
-    c.ib = -B * idet;
-    c.ic = A * idet;
-    int k = (int)th[7];
-    k = k < 0 ? 0 : (k > P.k_max ? P.k_max : k);
-    const int npick = n_picks(P, k);
-    const uint32_t pix = (uint32_t)(y * v.W + x);
-    const uint32_t cs = (uint32_t)(kCand * S.spp);
-    const uint32_t inv_spp = (65536u + (uint32_t)S.spp - 1u) / (uint32_t)S.spp;
-    const int own = (ly + kR) * SW + (lx + kR);
-    for (int s = 0; s < S.spp; ++s) nll_visit(c, lds[s * SA + own], a);
-    uint4 w4 = make_uint4(0, 0, 0, 0);
-    for (int m = 0; m < npick; ++m) {
-      if ((m & 7) == 0) w4 = philox4x32_10(pix, P.frame, (1u << 16) | (uint32_t)(m >> 3), P.view, P.key0, P.key1);
-      nll_visit(c, lds[pick_entry<SA, SW>(w4, m, cs, inv_spp, (uint32_t)S.spp, own)], a);
-    }
-    const float sc = grad_out ? grad_out[idx] : 1.0f;
-    gr[0] = sc * a.gmx;
-    gr[1] = sc * a.gmy;
-    gr[2] = sc * 2.0f * fmaf(a.gxx, l11, a.gxy * l21);
-    gr[3] = sc * 2.0f * fmaf(a.gxy, l11, a.gyy * l21);
-    gr[4] = sc * 2.0f * (a.gyy * l22);
-    gr[5] = sc * a.gl;
-  }
-  if (grad) {
-#pragma unroll
-    for (int ch = 0; ch < 8; ++ch) grad[ch * plane + idx] = gr[ch];
-  }
-  if (nll) nll[idx] = a.loss;
+  build_em_pick_table<TW, TH, TWO>(lds, S.spp);
+  EmInput<TW, TH> R;
+  em_load(v, S, op, tx0, ty0, R);
+  if constexpr (TWO)
+    em_tile2(P, v, S, op, tx0, ty0, (int)blockIdx.x, lds, sh, R);
+  else
+    em_tile(P, v, S, op, 1, tx0, ty0, (int)blockIdx.x, lds, sh, R);
 }
 
 // ---------------------------------------------------------------------------
@@ -1477,12 +1508,13 @@ __global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(TH == 2 
   const int tx0 = (l % bv.em_tiles_x) * TW, ty0 = (l / bv.em_tiles_x) * TH;
   const ParamsK P = batch_params(hd->base, bv);
   build_em_pick_table<TW, TH, TWO>(lds, bv.S.spp);
+  const EmOp<TG> op{(TG *)bv.gout};
   EmInput<TW, TH> R;
-  em_load(bv.cur, bv.S, (const TG *)bv.gout, tx0, ty0, R);
-  if (TWO)
-    em_tile2<TG, TW, TH>(P, bv.cur, bv.S, (TG *)bv.gout, tx0, ty0, (int)blockIdx.x, lds, sh, R);
+  em_load(bv.cur, bv.S, op, tx0, ty0, R);
+  if constexpr (TWO)
+    em_tile2(P, bv.cur, bv.S, op, tx0, ty0, (int)blockIdx.x, lds, sh, R);
   else
-    em_tile<TG, TW, TH>(P, bv.cur, bv.S, (TG *)bv.gout, 1, tx0, ty0, (int)blockIdx.x, lds, sh, R);
+    em_tile(P, bv.cur, bv.S, op, 1, tx0, ty0, (int)blockIdx.x, lds, sh, R);
 }
 
 // Philox words for given counters (diagnostic entry).

@@ -245,25 +245,29 @@ pg_status launch_em(Tile t, const ParamsK &P, const ViewK &v, const SamplesK &S,
   return launch_em_t<TG, 64, 2>(P, v, S, g, iters, batch, st);
 }
 
-template <int TW, int TH>
-void launch_nll_t(const ParamsK &P, const ViewK &v, const SamplesK &S, const float *theta, const float *go,
-                  float *grad, float *nll, hipStream_t st) {
+template <int TW, int TH, bool LOSS, bool GRAD>
+void launch_nll_t(const ParamsK &P, const ViewK &v, const SamplesK &S, const NllOp<LOSS, GRAD> &op, hipStream_t st) {
   const int tx = (v.W + TW - 1) / TW, ty = (v.H + TH - 1) / TH;
   const int n = tx * ty;
-  const size_t lds = (size_t)(TW + 2 * kR) * (TH + 2 * kR) * S.spp * sizeof(float4);
-  hipLaunchKernelGGL((k_nll<TW, TH>), dim3(n), dim3(TW * TH), lds, st, P, v, S, theta, go, grad, nll, tx, n);
+  const bool two = em_two_pass(S.spp, 0, 0);
+  const size_t lds = tile_lds(Tile{TW, TH}, S.spp, two);
+  if (two)
+    hipLaunchKernelGGL((k_nll<TW, TH, LOSS, GRAD, true>), dim3(n), dim3(TW * TH), lds, st, P, v, S, op, tx, n);
+  else
+    hipLaunchKernelGGL((k_nll<TW, TH, LOSS, GRAD, false>), dim3(n), dim3(TW * TH), lds, st, P, v, S, op, tx, n);
 }
 
-void launch_nll(Tile t, const ParamsK &P, const ViewK &v, const SamplesK &S, const float *theta,
-                const float *go, float *grad, float *nll, hipStream_t st) {
-  if (t.w == 32 && t.h == 8) launch_nll_t<32, 8>(P, v, S, theta, go, grad, nll, st);
-  else if (t.w == 16 && t.h == 16) launch_nll_t<16, 16>(P, v, S, theta, go, grad, nll, st);
-  else if (t.w == 64 && t.h == 4) launch_nll_t<64, 4>(P, v, S, theta, go, grad, nll, st);
-  else if (t.w == 32 && t.h == 4) launch_nll_t<32, 4>(P, v, S, theta, go, grad, nll, st);
-  else if (t.w == 16 && t.h == 8) launch_nll_t<16, 8>(P, v, S, theta, go, grad, nll, st);
-  else if (t.w == 32 && t.h == 16) launch_nll_t<32, 16>(P, v, S, theta, go, grad, nll, st);
-  else if (t.w == 64 && t.h == 8) launch_nll_t<64, 8>(P, v, S, theta, go, grad, nll, st);
-  else launch_nll_t<64, 2>(P, v, S, theta, go, grad, nll, st);
+template <bool LOSS, bool GRAD>
+void launch_nll(Tile t, const ParamsK &P, const ViewK &v, const SamplesK &S, const NllOp<LOSS, GRAD> &op,
+                hipStream_t st) {
+  if (t.w == 32 && t.h == 8) launch_nll_t<32, 8>(P, v, S, op, st);
+  else if (t.w == 16 && t.h == 16) launch_nll_t<16, 16>(P, v, S, op, st);
+  else if (t.w == 64 && t.h == 4) launch_nll_t<64, 4>(P, v, S, op, st);
+  else if (t.w == 32 && t.h == 4) launch_nll_t<32, 4>(P, v, S, op, st);
+  else if (t.w == 16 && t.h == 8) launch_nll_t<16, 8>(P, v, S, op, st);
+  else if (t.w == 32 && t.h == 16) launch_nll_t<32, 16>(P, v, S, op, st);
+  else if (t.w == 64 && t.h == 8) launch_nll_t<64, 8>(P, v, S, op, st);
+  else launch_nll_t<64, 2>(P, v, S, op, st);
 }
 
 LightsK to_k(const pg_lights *l) {
@@ -593,12 +597,21 @@ pg_status pg_nll_backward(const pg_params *p, const pg_view *v, const pg_samples
     return st;
   if (!theta) return fail(PG_ERR_ARG, "theta is NULL");
   if (!grad_theta && !nll) return fail(PG_ERR_ARG, "nothing to compute: grad_theta and nll are NULL");
+  // a requested tile is held to the single-pass tile's LDS limit, whichever
+  // tile runs (the two-pass one never needs more)
   Tile t;
   if ((st = pick_tile(p, in->spp, t))) return st;
+  if (p->tile_w == 0 && p->tile_h == 0) t = default_tile(in->spp, em_two_pass(in->spp, 0, 0));
   const ParamsK P = to_k(p);
   const ViewK V = to_k(v);
   const SamplesK S = to_k(in);
-  launch_nll(t, P, V, S, theta, grad_out, grad_theta, nll, (hipStream_t)stream);
+  hipStream_t s = (hipStream_t)stream;
+  if (!grad_theta)
+    launch_nll(t, P, V, S, NllOp<true, false>{theta, grad_out, grad_theta, nll}, s);
+  else if (!nll)
+    launch_nll(t, P, V, S, NllOp<false, true>{theta, grad_out, grad_theta, nll}, s);
+  else
+    launch_nll(t, P, V, S, NllOp<true, true>{theta, grad_out, grad_theta, nll}, s);
   return check_launch("pg_nll_backward");
 }
 

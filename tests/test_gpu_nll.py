@@ -10,7 +10,7 @@ import torch
 import oracle as O
 import paper_2112_09728_amd as pg
 from paper_2112_09728_amd import workload as wl
-from pgtest import dev, gpu_view, host, records_host
+from pgtest import dev, gpu_view, host, random_gamma, records_host
 
 pytestmark = [pytest.mark.gpu,
               pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
@@ -139,3 +139,36 @@ def test_gradient_fit_reaches_batch_em_likelihood():
     say(f"  summed NLL: EM(16) {total_em:.2f}  gradient fit start {hist[0]:.2f} end {hist[-1]:.2f}")
     assert hist[-1] < hist[0]
     assert hist[-1] <= total_em + 0.01 * abs(total_em)
+
+
+@pytest.mark.parametrize("W,H,spp", [(1, 1, 1), (33, 9, 2), (31, 17, 3), (17, 16, 4), (45, 33, 5), (70, 19, 8)])
+def test_nll_of_trained_records_at_tile_edges(W, H, spp):
+    """Remainders of the training tile (32x8 up to spp 3, 16x16 above), lists of
+    every length (k 0 to 16, records of a guided frame), the loss and the
+    gradient each on its own, and pixels that train nothing; the bounds are
+    those of the frame-0 comparison above."""
+    say(f"case: nll tile edges {W}x{H} spp {spp}")
+    seed = 9100 + W + spp
+    scene = wl.make_scene(W, H, seed)
+    rng = np.random.default_rng(seed)
+    p = pg.params(seed, frame=3)
+    view = gpu_view(scene)
+    s = pg.Samples(spp, H, W)
+    pg.sample_mis(p, view, dev(random_gamma(H, W, rng, k_lo=0)), s)
+    pg.light_field(pg.lights_struct(scene["lights"], float(scene["ambient"])), view, dev(scene["vis"]), s)
+    th = _theta(H, W, rng)
+    th[7] = rng.integers(0, 17, (H, W))
+    go = rng.uniform(0.5, 2.0, (H, W)).astype(np.float32)
+    nll, grad = pg.nll_backward(p, view, s, dev(th), grad_out=dev(go))
+    loss_only, _ = pg.nll_backward(p, view, s, dev(th), want_grad=False)
+    _, grad_only = pg.nll_backward(p, view, s, dev(th), grad_out=dev(go), want_nll=False)
+    torch.cuda.synchronize()
+    nll_o, grad_o = O.nll(O.params(seed, frame=3), O.OView(scene), records_host(s), th, grad_out=go)
+    idle = (scene["roughness"] < np.float32(0.1))
+    for n, g in ((host(nll), host(grad)), (host(loss_only), host(grad_only))):
+        en = np.abs(n - nll_o) / (np.abs(nll_o) + 1e-3 * (np.abs(nll_o).max() + 1e-30))
+        assert en.max() <= 1e-4
+        for c in range(6):
+            e = np.abs(g[c] - grad_o[c]) / (np.abs(grad_o[c]) + 1e-3 * (np.abs(grad_o[c]).max() + 1e-30))
+            assert np.quantile(e, 0.99) <= 1e-4 and e.max() <= 1e-3, c
+        assert (g[6:] == 0).all() and (n[idle] == 0).all() and (g[:, idle] == 0).all()
