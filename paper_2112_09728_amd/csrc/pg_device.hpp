@@ -8,6 +8,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace pgk {
 
 constexpr float kPi = 3.14159265358979323846f;
@@ -46,12 +48,32 @@ __device__ __forceinline__ float div_pos(float x, float d) {
 // Row offset y * pitch of a pixel: both below 2^24 (the library bounds the
 // sides and the pitch), so the full-rate 24-bit multiply gives it.
 __device__ __forceinline__ int row_off(int y, int pitch) { return (int)__umul24((uint32_t)y, (uint32_t)pitch); }
-// Element i of an array whose base is uniform across the wave, with i taken
-// as an unsigned 32-bit offset: the access then uses the scalar-base plus
-// vector-offset form instead of 64-bit address arithmetic in every lane.
+// Element i of an array whose base is uniform across the wave.  The byte
+// offset is formed in 32 bits, so that the access takes the scalar-base plus
+// vector-offset form: with p[i] the compiler cannot rule out that 4 i exceeds
+// 32 bits and forms a 64-bit address in every lane (one more instruction and
+// register pair per access).  Every plane group that is indexed from one base
+// stays below 2^32 bytes: the library bounds 24 * pitch * height, and 3 n *
+// pitch * height for n directions a pixel, to 2^31 elements, so n * plane
+// floats take less than 2.9e9 bytes.
 template <typename T>
 __device__ __forceinline__ T &at(T *p, int i) {
-  return p[(uint32_t)i];
+  using Byte = std::conditional_t<std::is_const_v<T>, const char, char>;
+  return *reinterpret_cast<T *>(reinterpret_cast<Byte *>(p) + (uint32_t)i * (uint32_t)sizeof(T));
+}
+// Four consecutive elements from any element on, in one access (the hardware
+// takes 16-byte loads at 4-byte and 4-byte loads at any alignment; the types
+// say so to the compiler).
+typedef float F4 __attribute__((ext_vector_type(4)));
+typedef F4 F4U __attribute__((aligned(4)));
+struct __attribute__((packed, aligned(1))) Byte4U {
+  uint32_t v;
+};
+__device__ __forceinline__ F4 load4(const float *p, int i) {
+  return *reinterpret_cast<const F4U *>(reinterpret_cast<const char *>(p) + (uint32_t)i * 4u);
+}
+__device__ __forceinline__ uint32_t load4(const uint8_t *p, int i) {
+  return reinterpret_cast<const Byte4U *>(p + (uint32_t)i)->v;
 }
 __device__ __forceinline__ float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
 

@@ -106,7 +106,7 @@ struct PixelIn {
 
 __device__ __forceinline__ PixelIn load_pixel(const ViewK &v, int idx) {
   const int plane = v.H * v.pitch;
-  return PixelIn{load3(v.n, plane, idx), load3(v.o, plane, idx), v.rough[idx]};
+  return PixelIn{load3(v.n, plane, idx), load3(v.o, plane, idx), at(v.rough, idx)};
 }
 
 template <typename TG>
@@ -122,12 +122,12 @@ __device__ __forceinline__ int reproject_pixel(const ParamsK &P, const ViewK &cu
   float zp = 0.0f, mx = 0.0f, my = 0.0f;
   bool keep = has_prev && guided;
   if (keep) {
-    zp = cur.z[idx];
+    zp = at(cur.z, idx);
     if (cur.mv) {
-      mx = cur.mv[idx];
-      my = cur.mv[plane + idx];
+      mx = at(cur.mv, idx);
+      my = at(cur.mv + plane, idx);
     }
-    if (cur.mask != nullptr && cur.mask[idx] != 0) keep = false;
+    if (cur.mask != nullptr && at(cur.mask, idx) != 0) keep = false;
   }
   int qx = 0, qy = 0;
   if (keep) {
@@ -143,7 +143,7 @@ __device__ __forceinline__ int reproject_pixel(const ParamsK &P, const ViewK &cu
   if (keep) {
     const int pplane = prev.H * prev.pitch;
     const int qidx = qy * prev.pitch + qx;
-    const float zq = prev.z[qidx];
+    const float zq = at(prev.z, qidx);
     const V3 nq = load3(prev.n, pplane, qidx);
     gamma_load(gprev, pplane, qidx, g);
     if (fabsf(zp - zq) > P.tau_z * zp) keep = false;
@@ -184,21 +184,21 @@ __global__ __launch_bounds__(256) void k_estimate(ParamsK P, ViewK v, SamplesK S
   const V3 n = load3(v.n, plane, idx), o = load3(v.o, plane, idx);
   float acc = 0.0f;
   if (dot3(n, o) > 0.0f) {
-    const Pixel px = make_pixel(P, n, o, v.rough[idx], v.alb[idx]);
+    const Pixel px = make_pixel(P, n, o, at(v.rough, idx), at(v.alb, idx));
     for (int s = 0; s < S.spp; ++s) {
       const int r = (s * v.H + y) * v.pitch + x;
-      const uint8_t code = S.strat[r];
-      const float D = S.pmix[r];
+      const uint8_t code = at(S.strat, r);
+      const float D = at(S.pmix, r);
       if (!(code == 1 || code == 2) || !(D > 0.0f)) continue;
-      const V3 l = to_local(px.f, normalized(V3{S.dir[r], S.dir[splane + r], S.dir[2 * splane + r]}));
+      const V3 l = to_local(px.f, normalized(load3(S.dir, splane, r)));
       if (l.z <= 0.0f) continue;
       float f, pb;
       brdf_eval(px, l, f, pb);
-      acc += f * S.L[r] * l.z / D;
+      acc += f * at(S.L, r) * l.z / D;
     }
     acc /= (float)S.spp;
   }
-  out[idx] = acc;
+  at(out, idx) = acc;
 }
 
 // Analytic incident radiance (stand-in for the trace).  For unit w and xi,
@@ -313,13 +313,13 @@ __device__ __forceinline__ void sample_pixel(const ParamsK &P, const ViewK &v, c
       D = 0.0f;
       pb = 0.0f;
     }
-    S.dir[rec] = w.x;
-    S.dir[splane + rec] = w.y;
-    S.dir[2 * splane + rec] = w.z;
-    S.pmix[rec] = D;
-    S.pb[rec] = pb;
-    S.strat[rec] = code;
-    if (Lt) S.L[rec] = (code == 1 || code == 2) ? light_radiance(*Lt, visbits, w) : 0.0f;
+    at(S.dir, rec) = w.x;
+    at(S.dir + splane, rec) = w.y;
+    at(S.dir + 2 * splane, rec) = w.z;
+    at(S.pmix, rec) = D;
+    at(S.pb, rec) = pb;
+    at(S.strat, rec) = code;
+    if (Lt) at(S.L, rec) = (code == 1 || code == 2) ? light_radiance(*Lt, visbits, w) : 0.0f;
   }
 }
 
@@ -334,7 +334,7 @@ __global__ __launch_bounds__(256) void k_reproject(ParamsK P, ViewK cur, ViewK p
   const int idx = y * cur.pitch + x;
   const int src = reproject_pixel(P, cur, prev, gprev, has_prev != 0, x, y, load_pixel(cur, idx), g);
   gamma_store(gout, cur.H * cur.pitch, idx, g);
-  if (src_index) src_index[idx] = src;
+  if (src_index) at(src_index, idx) = src;
 }
 
 template <typename TG>
@@ -360,7 +360,7 @@ __device__ __forceinline__ void reproject_sample_pixel(const ParamsK &P, const V
                                                        const uint8_t *vis = nullptr) {
   const int idx = y * cur.pitch + x;
   const PixelIn pi = load_pixel(cur, idx);
-  const uint32_t visbits = vis ? vis[idx] : 0u;
+  const uint32_t visbits = vis ? at(vis, idx) : 0u;
   float g[8];
   reproject_pixel(P, cur, prev, gprev, has_prev, x, y, pi, g);
   float gs[8];
@@ -400,7 +400,7 @@ __global__ __launch_bounds__(256) void k_pdf(ParamsK P, ViewK v, const TG *__res
   gamma_load(gamma, plane, idx, g);
   const V3 n = load3(v.n, plane, idx);
   const V3 o = load3(v.o, plane, idx);
-  const float rough = v.rough[idx];
+  const float rough = at(v.rough, idx);
   const bool valid = dot3(n, o) > 0.0f;
   const bool guided = valid && rough >= P.rough_min;
   const float pe = (guided && g[7] >= 1.0f) ? g[5] : 0.0f;
@@ -408,7 +408,7 @@ __global__ __launch_bounds__(256) void k_pdf(ParamsK P, ViewK v, const TG *__res
   const Gauss G = gauss_setup(g[0], g[1], g[2], g[3], g[4], P.eps);
   for (int j = 0; j < n_per_px; ++j) {
     const int r = (j * v.H + y) * v.pitch + x;
-    const V3 w = V3{dir[r], dir[dplane + r], dir[2 * dplane + r]};
+    const V3 w = load3(dir, dplane, r);
     float pg = 0.0f, pb = 0.0f;
     const float ww = dot3(w, w);
     if (valid && ww > 0.0f) {
@@ -420,9 +420,9 @@ __global__ __launch_bounds__(256) void k_pdf(ParamsK P, ViewK v, const TG *__res
         pb = brdf_pdf_only(px, l);
       }
     }
-    pmix[r] = fmaf(pe, pg, (1.0f - pe) * pb);
-    if (pguide) pguide[r] = pg;
-    if (pbrdf) pbrdf[r] = pb;
+    at(pmix, r) = fmaf(pe, pg, (1.0f - pe) * pb);
+    if (pguide) at(pguide, r) = pg;
+    if (pbrdf) at(pbrdf, r) = pb;
   }
 }
 
@@ -435,13 +435,11 @@ __global__ __launch_bounds__(256) void k_light(LightsK Lt, ViewK v, const uint8_
   const int plane = v.H * v.pitch;
   const int idx = y * v.pitch + x;
   const int splane = S.spp * plane;
-  const uint32_t bits = vis[idx];
+  const uint32_t bits = at(vis, idx);
   for (int s = 0; s < S.spp; ++s) {
     const int r = (s * v.H + y) * v.pitch + x;
-    const uint8_t code = S.strat[r];
-    S.L[r] = (code == 1 || code == 2)
-                 ? light_radiance(Lt, bits, V3{S.dir[r], S.dir[splane + r], S.dir[2 * splane + r]})
-                 : 0.0f;
+    const uint8_t code = at(S.strat, r);
+    at(S.L, r) = (code == 1 || code == 2) ? light_radiance(Lt, bits, load3(S.dir, splane, r)) : 0.0f;
   }
 }
 
@@ -454,54 +452,141 @@ __global__ __launch_bounds__(256) void k_light(LightsK Lt, ViewK v, const uint8_
 // outside the image (such records add nothing to any sum, which is the same
 // as leaving them out of the training set).
 
+// A tile's records are read four at a time: the window of TW + 8 columns from
+// tx0 - 4 on (the halo of 3 and one more on either side) is whole groups of
+// four, whose 16-byte loads start at multiples of 16 bytes in a plane of
+// aligned rows.  One record a lane, as before, started 12 bytes off those
+// multiples and split a wave over three rows: the address units spent 23
+// cycles on each such load (4 on an aligned one), half of the two-pass
+// kernel's time at spp 8, and the plane-by-plane rounds their latency on top.
 template <int TW, int TH>
-__device__ __forceinline__ void stage_records(const ViewK &v, const SamplesK &S, float4 *lds, int tx0,
-                                              int ty0, int s0 = 0) {
-  constexpr int SW = TW + 2 * kR, SH = TH + 2 * kR, SA = SW * SH, NT = TW * TH;
-  constexpr int IT = (SA + NT - 1) / NT;  // records of one sample plane per thread
-  const int plane = v.H * v.pitch;
-  const int splane = S.spp * plane;
-  int gi[IT];
-  bool in[IT];
-#pragma unroll
-  for (int i = 0; i < IT; ++i) {
-    const int e = threadIdx.x + i * NT;
-    // e < 2^13, so the float quotient floors exactly
-    const int sy = (int)(((float)e + 0.5f) * (1.0f / SW));
-    const int sx = e - (int)__umul24((uint32_t)sy, (uint32_t)SW);
-    const int gx = tx0 - kR + sx, gy = ty0 - kR + sy;
-    in[i] = e < SA && gx >= 0 && gy >= 0 && gx < v.W && gy < v.H;
-    gi[i] = row_off(gy, v.pitch) + gx;  // used only inside the image
+struct Window {
+  static constexpr int SW = TW + 8, G = SW / 4, SH = TH + 2 * kR, NG = SH * G, NT = TW * TH;
+  static_assert(TW % 4 == 0 && NG % 2 == 0, "groups of four, in pairs");
+};
+
+// Group `item` of the records of sample planes s0, s0 + 1, ... of a tile:
+// four records of one row.
+struct RecordGroup {
+  F4 x, y, z, l, p;
+  uint32_t st;  // the four strategy codes
+  uint32_t in;  // bits 0-3: record j lies inside the image; from bit 8 on: the
+                // records by which the loads start before the group
+};
+
+// Plane, row and group column of an item (item < 2^13: the float quotients
+// floor exactly).
+template <int TW, int TH>
+__device__ __forceinline__ void item_place(int item, int &s, int &sy, int &g) {
+  using Wn = Window<TW, TH>;
+  s = (int)(((float)item + 0.5f) * (1.0f / Wn::NG));
+  const int r = item - (int)__umul24((uint32_t)s, (uint32_t)Wn::NG);
+  sy = (int)(((float)r + 0.5f) * (1.0f / Wn::G));
+  g = r - (int)__umul24((uint32_t)sy, (uint32_t)Wn::G);
+}
+
+// Issue the loads of an item (no use of the results here): strategy and
+// density (KEY) and direction and radiance (REC).  The loads take no branch:
+// a group outside the image reads the planes' first records, and one that
+// would cross the end of the planes (its row's end, in the last row of an
+// image whose pitch is no multiple of 4) starts up to three records early.
+// The planes must hold four records or more in all (stage_few otherwise).
+template <int TW, int TH, bool KEY, bool REC>
+__device__ __forceinline__ void load_group(const ViewK &v, const SamplesK &S, int tx0, int ty0, int s0, int item,
+                                           RecordGroup &q) {
+  int s, sy, g;
+  item_place<TW, TH>(item, s, sy, g);
+  const int plane = v.H * v.pitch, splane = S.spp * plane;
+  const int gx = tx0 - 4 + 4 * g, gy = ty0 - kR + sy;
+  const int n = min(v.W - gx, 4);  // records before the right edge
+  const bool in = gy >= 0 && gy < v.H && gx >= 0 && n > 0;
+  const int o0 = in ? (s0 + s) * plane + row_off(gy, v.pitch) + gx : 0;
+  const int o = min(o0, splane - 4);
+  q.in = (in ? (1u << n) - 1u : 0u) | (uint32_t)(o0 - o) << 8;
+  if (KEY) q.st = load4(S.strat, o);
+  q.p = load4(S.pb, o);
+  if (REC) {
+    q.x = load4(S.dir, o);
+    q.y = load4(S.dir + splane, o);
+    q.z = load4(S.dir + 2 * splane, o);
+    q.l = load4(S.L, o);
   }
-  for (int s = s0; s < S.spp; ++s) {
-    // every load of this sample plane is issued before the first use
-    uint8_t st[IT];
-    float px[IT], py[IT], pz[IT], pl[IT], pp[IT];
-#pragma unroll
-    for (int i = 0; i < IT; ++i) {
-      st[i] = 0;
-      px[i] = py[i] = pz[i] = pl[i] = pp[i] = 0.0f;
-      if (in[i]) {
-        const int o = s * plane + gi[i];
-        st[i] = at(S.strat, o);
-        pp[i] = at(S.pb, o);
-        px[i] = at(S.dir, o);
-        py[i] = at(S.dir + splane, o);
-        pz[i] = at(S.dir + 2 * splane, o);
-        pl[i] = at(S.L, o);
-      }
+}
+
+// A group at its place, once its loads have come back.  (The barrier keeps the
+// compiler from testing values, and so awaiting them, right after their own
+// loads, before it issues others.)
+template <bool REC>
+__device__ __forceinline__ void settle(RecordGroup &q) {
+  asm volatile("" : "+v"(q.st), "+v"(q.p));
+  for (uint32_t d = q.in >> 8; d > 0; --d) {
+    q.st >>= 8;
+    q.p = q.p.yzww;
+    if (REC) {
+      q.x = q.x.yzww;
+      q.y = q.y.yzww;
+      q.z = q.z.yzww;
+      q.l = q.l.yzww;
     }
+  }
+}
+
+// Whether record j of a group trains: a BRDF-strategy sample inside the image
+// (its density is a normal number: at least s_d cos/pi of a valid draw, or
+// the GGX density of the drawn normal).
+__device__ __forceinline__ bool group_valid(const RecordGroup &q, int j) {
+  return ((q.in >> j) & 1u) != 0u && ((q.st >> (8 * j)) & 0xFFu) == 1u && q.p[j] > 0.0f;
+}
+__device__ __forceinline__ float group_weight(const RecordGroup &q, int j) {
+  return q.l[j] * frcp(fmaxf(q.p[j], 1.17549435e-38f));
+}
+
+// A group's records to the LDS of the single-pass tile, [spp][TH+6][TW+6]:
+// L / p_src is 0 for a record that does not train (and the rest of it is
+// then never read).
+template <int TW, int TH>
+__device__ __forceinline__ void put_group(float4 *lds, int item, RecordGroup &q) {
+  constexpr int SW = TW + 2 * kR, SA = SW * (TH + 2 * kR), G = Window<TW, TH>::G;
+  int s, sy, g;
+  item_place<TW, TH>(item, s, sy, g);
+  const int e = s * SA + (int)__umul24((uint32_t)sy, (uint32_t)SW) + 4 * g - 1;
+  settle<true>(q);
 #pragma unroll
-    for (int i = 0; i < IT; ++i) {
-      const int e = threadIdx.x + i * NT;
-      if (IT * NT == SA || e < SA) {
-        // a BRDF sample's density is a normal number (at least s_d cos/pi of
-        // a valid draw, or the GGX density of the drawn normal)
-        const bool ok = st[i] == 1 && pp[i] > 0.0f;
-        lds[s * SA + e] = ok ? make_float4(px[i], py[i], pz[i], pl[i] * frcp(fmaxf(pp[i], 1.17549435e-38f)))
-                             : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      }
+  for (int j = 0; j < 4; ++j)
+    if ((j > 0 || g > 0) && (j < 3 || g < G - 1))
+      lds[e + j] = make_float4(q.x[j], q.y[j], q.z[j], group_valid(q, j) ? group_weight(q, j) : 0.0f);
+}
+
+// The single-pass tile's records from item `begin` on (all sample planes).
+template <int TW, int TH>
+__device__ __forceinline__ void stage_records(const ViewK &v, const SamplesK &S, float4 *lds, int tx0, int ty0,
+                                              int begin) {
+  const int n = S.spp * Window<TW, TH>::NG;
+  for (int i = begin + (int)threadIdx.x; i < n; i += TW * TH) {
+    RecordGroup q;
+    load_group<TW, TH, true, true>(v, S, tx0, ty0, 0, i, q);
+    put_group<TW, TH>(lds, i, q);
+  }
+}
+
+// Sample planes of fewer than four records in all (an image of one to three
+// pixels) hold no group: their records one by one.
+__device__ __forceinline__ bool few_records(const ViewK &v, const SamplesK &S) { return S.spp * v.H * v.pitch < 4; }
+template <int TW, int TH>
+__device__ __forceinline__ void stage_few(const ViewK &v, const SamplesK &S, float4 *lds, int tx0, int ty0) {
+  constexpr int SW = TW + 2 * kR, SA = SW * (TH + 2 * kR);
+  const int plane = v.H * v.pitch, splane = S.spp * plane;
+  for (int i = threadIdx.x; i < S.spp * SA; i += TW * TH) {
+    const int s = i / SA, e = i - s * SA, gx = tx0 - kR + e % SW, gy = ty0 - kR + e / SW;
+    float4 r = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (gx >= 0 && gy >= 0 && gx < v.W && gy < v.H) {
+      const int o = s * plane + row_off(gy, v.pitch) + gx;
+      const float p = at(S.pb, o);
+      if (at(S.strat, o) == 1 && p > 0.0f)
+        r = make_float4(at(S.dir, o), at(S.dir + splane, o), at(S.dir + 2 * splane, o),
+                        at(S.L, o) * frcp(fmaxf(p, 1.17549435e-38f)));
     }
+    lds[i] = r;
   }
 }
 
@@ -610,18 +695,19 @@ __device__ __forceinline__ void build_pick_table(int16_t *tab, int spp) {
   }
 }
 
-// The two-pass training tile (online EM from spp 4) holds the records of
-// the first ceil(spp/2) sample planes at a time; its dynamic LDS: those
-// records [PG][SA] float4, a validity bit for every candidate record of all
-// planes [spp SA] (bytes rounded up to 16), the lists [spp+20][w h] uint16,
-// the pick table and, per pixel, the list's entries in the first pass
-// [w h] uint8.
+// The two-pass training tile (from spp 4) holds the records of the first
+// ceil(spp/2) sample planes at a time; its dynamic LDS: those records
+// [PG][TH+6][TW+8] float4, a validity bit for every candidate record of all
+// planes [spp][TH+6][TW+8], the lists [spp+20][w h] uint16, the pick table
+// and, per pixel, the list's entries in the first pass [w h] uint8.  (Rows of
+// whole groups of four: two lanes' groups are one byte of bits.)
 __host__ __device__ constexpr int em2_planes(int spp) { return (spp + 1) >> 1; }
+__host__ __device__ constexpr int em2_stride(int tw, int th) { return (tw + 8) * (th + 2 * kR); }
 __host__ __device__ constexpr size_t em2_bits_bytes(int tw, int th, int spp) {
-  return (((size_t)spp * (tw + 2 * kR) * (th + 2 * kR) + 31) / 32 * 4 + 15) & ~(size_t)15;
+  return ((size_t)spp * em2_stride(tw, th) / 8 + 15) & ~(size_t)15;
 }
 __host__ __device__ constexpr size_t em2_lds_front(int tw, int th, int spp) {
-  return (size_t)(tw + 2 * kR) * (th + 2 * kR) * em2_planes(spp) * 16 + em2_bits_bytes(tw, th, spp) +
+  return (size_t)em2_stride(tw, th) * em2_planes(spp) * 16 + em2_bits_bytes(tw, th, spp) +
          (size_t)(spp + 20) * tw * th * 2 + (size_t)pick_table_bytes(spp) + (size_t)tw * th;
 }
 
@@ -632,7 +718,7 @@ template <int TW, int TH, bool TWO>
 __device__ __forceinline__ uint16_t *em_lists(float4 *lds, int spp) {
   constexpr int SA = (TW + 2 * kR) * (TH + 2 * kR);
   if (TWO)
-    return reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(lds + em2_planes(spp) * SA) +
+    return reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(lds + em2_planes(spp) * em2_stride(TW, TH)) +
                                         em2_bits_bytes(TW, TH, spp));
   return reinterpret_cast<uint16_t *>(lds + spp * SA);
 }
@@ -641,7 +727,7 @@ __device__ __forceinline__ uint16_t *em_lists(float4 *lds, int spp) {
 // every thread before em_tile; em_tile's first barrier publishes it).
 template <int TW, int TH, bool TWO = false>
 __device__ __forceinline__ void build_em_pick_table(float4 *lds, int spp) {
-  constexpr int SW = TW + 2 * kR, SA = SW * (TH + 2 * kR), NT = TW * TH;
+  constexpr int SW = TW + (TWO ? 8 : 2 * kR), SA = SW * (TH + 2 * kR), NT = TW * TH;
   build_pick_table<SA, SW>(reinterpret_cast<int16_t *>(em_lists<TW, TH, TWO>(lds, spp) + (spp + 20) * NT), spp);
 }
 
@@ -831,56 +917,39 @@ __host__ __device__ constexpr size_t em_lds_front(int tw, int th, int spp) {
          (size_t)pick_table_bytes(spp);
 }
 
-// One thread's share of a training tile's inputs, held in registers while
-// the loads are in flight: what decides its pixel's candidate count (epoch,
-// normal, view direction, roughness; natural order) and its records of
-// sample plane 0.
-template <int TW, int TH>
-struct EmInput {
-  static constexpr int SW = TW + 2 * kR, SA = SW * (TH + 2 * kR), NT = TW * TH, IT = (SA + NT - 1) / NT;
+// What decides a pixel's candidate count (epoch, normal, view direction,
+// roughness; natural order).
+struct EmPixel {
   float k, rough;
   V3 n, o;
-  uint32_t st[IT];
-  float px[IT], py[IT], pz[IT], pl[IT], pp[IT];
+};
+
+template <typename Op>
+__device__ __forceinline__ EmPixel em_load_pixel(const ViewK &v, const Op &op, int tx0, int ty0, int tw) {
+  const int plane = v.H * v.pitch;
+  // clamped into the image, so that the loads need no branch (a branch made
+  // the compiler await the epoch inside it, before anything else was issued);
+  // the caller masks what lies outside
+  const int x0 = min(tx0 + (int)threadIdx.x % tw, v.W - 1), y0 = min(ty0 + (int)threadIdx.x / tw, v.H - 1);
+  const int idx0 = row_off(y0, v.pitch) + x0;
+  return EmPixel{op.epoch(plane, idx0), at(v.rough, idx0), load3(v.n, plane, idx0), load3(v.o, plane, idx0)};
+}
+
+// A single-pass tile's inputs in flight: a thread's pixel and its first group
+// of records.
+template <int TW, int TH>
+struct EmInput {
+  EmPixel q;
+  RecordGroup r;
 };
 
 // Issue the loads of a tile's inputs (no use of the results here).
 template <typename Op, int TW, int TH>
 __device__ __forceinline__ void em_load(const ViewK &v, const SamplesK &S, const Op &op, int tx0, int ty0,
                                         EmInput<TW, TH> &R) {
-  using In = EmInput<TW, TH>;
-  const int plane = v.H * v.pitch;
-  const int t = threadIdx.x;
-  const int x0 = tx0 + t % TW, y0 = ty0 + t / TW;
-  R.k = R.rough = 0.0f;
-  R.n = R.o = V3{0, 0, 0};
-  if (x0 < v.W && y0 < v.H) {
-    const int idx0 = row_off(y0, v.pitch) + x0;
-    R.k = op.epoch(plane, idx0);
-    R.rough = at(v.rough, idx0);
-    R.n = load3(v.n, plane, idx0);
-    R.o = load3(v.o, plane, idx0);
-  }
-  const int splane = S.spp * plane;
-#pragma unroll
-  for (int i = 0; i < In::IT; ++i) {
-    const int e = t + i * In::NT;
-    // e < 2^13, so the float quotient floors exactly
-    const int sy = (int)(((float)e + 0.5f) * (1.0f / In::SW));
-    const int sx = e - (int)__umul24((uint32_t)sy, (uint32_t)In::SW);
-    const int gx = tx0 - kR + sx, gy = ty0 - kR + sy;
-    R.st[i] = 0;
-    R.px[i] = R.py[i] = R.pz[i] = R.pl[i] = R.pp[i] = 0.0f;
-    if (e < In::SA && gx >= 0 && gy >= 0 && gx < v.W && gy < v.H) {
-      const int o = row_off(gy, v.pitch) + gx;
-      R.st[i] = at(S.strat, o);
-      R.pp[i] = at(S.pb, o);
-      R.px[i] = at(S.dir, o);
-      R.py[i] = at(S.dir + splane, o);
-      R.pz[i] = at(S.dir + 2 * splane, o);
-      R.pl[i] = at(S.L, o);
-    }
-  }
+  R.q = em_load_pixel(v, op, tx0, ty0, TW);
+  if ((int)threadIdx.x < S.spp * Window<TW, TH>::NG && !few_records(v, S))
+    load_group<TW, TH, true, true>(v, S, tx0, ty0, 0, (int)threadIdx.x, R.r);
 }
 
 // What a training tile does with each pixel's training set, as a type `Op`:
@@ -974,8 +1043,8 @@ __device__ __forceinline__ void tile_write_back(const Op &op, float *wb, int me,
 template <typename Op, int TW, int TH, bool STALE = false, bool BATCH = false>
 __device__ __forceinline__ void em_tile(const ParamsK &P, const ViewK &v, const SamplesK &S, const Op &op,
                                         int iterations, int tx0, int ty0, int rot, float4 *lds,
-                                        EmShared<TW * TH> &sh, const EmInput<TW, TH> &R) {
-  constexpr int SW = TW + 2 * kR, SH = TH + 2 * kR, SA = SW * SH, NT = TW * TH, IT = EmInput<TW, TH>::IT;
+                                        EmShared<TW * TH> &sh, EmInput<TW, TH> &R) {
+  constexpr int SA = (TW + 2 * kR) * (TH + 2 * kR), NT = TW * TH;
   uint16_t *list = reinterpret_cast<uint16_t *>(lds + S.spp * SA);
   float *wb = reinterpret_cast<float *>(lds);  // write-back area, once the records are no longer read
   const int plane = v.H * v.pitch;
@@ -984,22 +1053,15 @@ __device__ __forceinline__ void em_tile(const ParamsK &P, const ViewK &v, const 
   const bool in_image = x0 < v.W && y0 < v.H;
   int16_t *ptab = reinterpret_cast<int16_t *>(list + (S.spp + 20) * NT);
   if (t < 2 * kMaxLen) (&sh.cnt[0][0])[t] = 0;
-  // plane-0 records to LDS
-#pragma unroll
-  for (int i = 0; i < IT; ++i) {
-    const int e = t + i * NT;
-    if (IT * NT == SA || e < SA) {
-      // a BRDF sample's density is a normal number (at least s_d cos/pi of a
-      // valid draw, or the GGX density of the drawn normal)
-      const bool ok = R.st[i] == 1 && R.pp[i] > 0.0f;
-      lds[e] = ok ? make_float4(R.px[i], R.py[i], R.pz[i], R.pl[i] * frcp(fmaxf(R.pp[i], 1.17549435e-38f)))
-                  : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    }
+  if (few_records(v, S)) {
+    stage_few<TW, TH>(v, S, lds, tx0, ty0);
+  } else {
+    if (t < S.spp * Window<TW, TH>::NG) put_group<TW, TH>(lds, t, R.r);
+    if (S.spp * Window<TW, TH>::NG > NT) stage_records<TW, TH>(v, S, lds, tx0, ty0, NT);
   }
-  if (S.spp > 1) stage_records<TW, TH>(v, S, lds, tx0, ty0, 1);
   // the number of candidates of this lane's pixel (0 when it is not trained)
   int ncand = 0;
-  if (in_image && dot3(R.n, R.o) > 0.0f && R.rough >= P.rough_min) ncand = S.spp + n_picks(P, (int)R.k);
+  if (in_image && dot3(R.q.n, R.q.o) > 0.0f && R.q.rough >= P.rough_min) ncand = S.spp + n_picks(P, (int)R.q.k);
   sh.work[t] = (uint8_t)ncand;
   __syncthreads();
   // lists: pixels by decreasing candidate count
@@ -1064,66 +1126,67 @@ __device__ __forceinline__ void em_tile(const ParamsK &P, const ViewK &v, const 
 // planes, and the same sums continue over them.  Each pass keeps the
 // training set's order, so the result does not depend on the tile shape.
 
-// Validity bits and (for planes below `pg`) records of sample planes
-// [s0, s1) of a tile; with `bits` false only records, placed at plane
-// s - s0.  Each thread's halo positions are computed once for all planes.
-template <int TW, int TH>
-__device__ __forceinline__ void stage2(const ViewK &v, const SamplesK &S, float4 *rec, uint32_t *vb, int tx0,
-                                       int ty0, int s0, int s1, int pg, bool bits) {
-  constexpr int SW = TW + 2 * kR, SH = TH + 2 * kR, SA = SW * SH, NT = TW * TH;
-  constexpr int IT = (SA + NT - 1) / NT;
-  const int plane = v.H * v.pitch;
-  const int splane = S.spp * plane;
-  int gi[IT];
-  bool in[IT];
+// A group's records (REC) and validity bits (KEY) to the LDS of the two-pass
+// tile: records at their own item, bits at `bit_item` (the same unless the
+// planes before are not among the items).  The lanes of a pair of groups,
+// neighbours in a wave, form one byte of bits.
+template <int TW, int TH, bool KEY, bool REC>
+__device__ __forceinline__ void put_group2(float4 *rec, uint8_t *vb, int item, int bit_item, RecordGroup &q) {
+  settle<REC>(q);
+  if (KEY) {
+    uint32_t b = 0u;
 #pragma unroll
-  for (int i = 0; i < IT; ++i) {
-    const int e = threadIdx.x + i * NT;
-    // e < 2^13, so the float quotient floors exactly
-    const int sy = (int)(((float)e + 0.5f) * (1.0f / SW));
-    const int sx = e - (int)__umul24((uint32_t)sy, (uint32_t)SW);
-    const int gx = tx0 - kR + sx, gy = ty0 - kR + sy;
-    in[i] = e < SA && gx >= 0 && gy >= 0 && gx < v.W && gy < v.H;
-    gi[i] = row_off(gy, v.pitch) + gx;  // used only inside the image
+    for (int j = 0; j < 4; ++j) b |= group_valid(q, j) ? 1u << j : 0u;
+    const uint32_t hi = (uint32_t)__shfl_down((int)b, 1, 64);
+    if ((item & 1) == 0) vb[bit_item >> 1] = (uint8_t)(b | (hi << 4));
   }
-  for (int s = s0; s < s1; ++s) {
-    const bool keep_rec = !bits || s < pg;
-    const int rs = bits ? s : s - s0;  // plane index in the records area
-    // every load of this sample plane is issued before the first use
-    uint8_t st[IT];
-    float px[IT], py[IT], pz[IT], pl[IT], pp[IT];
+  if (REC) {
 #pragma unroll
-    for (int i = 0; i < IT; ++i) {
-      st[i] = 0;
-      px[i] = py[i] = pz[i] = pl[i] = pp[i] = 0.0f;
-      if (in[i]) {
-        const int o = s * plane + gi[i];
-        st[i] = at(S.strat, o);
-        pp[i] = at(S.pb, o);
-        if (keep_rec) {
-          px[i] = at(S.dir, o);
-          py[i] = at(S.dir + splane, o);
-          pz[i] = at(S.dir + 2 * splane, o);
-          pl[i] = at(S.L, o);
-        }
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < IT; ++i) {
-      const int e = threadIdx.x + i * NT;
-      if (IT * NT == SA || e < SA) {
-        // a BRDF sample's density is a normal number (at least s_d cos/pi of
-        // a valid draw, or the GGX density of the drawn normal)
-        const bool ok = st[i] == 1 && pp[i] > 0.0f;
-        if (keep_rec)
-          rec[rs * SA + e] = ok ? make_float4(px[i], py[i], pz[i], pl[i] * frcp(fmaxf(pp[i], 1.17549435e-38f)))
-                                : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (bits && ok) {
-          const int b = s * SA + e;
-          atomicOr(&vb[b >> 5], 1u << (b & 31));
-        }
-      }
-    }
+    for (int j = 0; j < 4; ++j)  // (a record whose bit is not set is never read)
+      rec[4 * item + j] = make_float4(q.x[j], q.y[j], q.z[j], group_weight(q, j));
+  }
+}
+
+// Staging of the two-pass tile: validity bits of every sample plane, and the
+// records of the first `pg`; then, in their place, those of the others.  A
+// first round holds two groups a thread in flight (42 registers), and with
+// them two of the planes that need bits alone; what is left (16 groups of 528
+// in a 16x16 tile at spp 7 and 8) follows one by one.  The first round is no
+// part of the loop: at a loop's head the compiler awaits what the round before
+// left in flight.
+template <int TW, int TH>
+__device__ __forceinline__ void stage2_first(const ViewK &v, const SamplesK &S, float4 *rec, uint8_t *vb, int tx0,
+                                             int ty0, int pg) {
+  constexpr int NT = TW * TH, NG = Window<TW, TH>::NG;
+  const int t = threadIdx.x, n = pg * NG, m = (S.spp - pg) * NG;
+  RecordGroup a, b, c, d;
+  if (t < n) load_group<TW, TH, true, true>(v, S, tx0, ty0, 0, t, a);
+  if (t + NT < n) load_group<TW, TH, true, true>(v, S, tx0, ty0, 0, t + NT, b);
+  if (t < m) load_group<TW, TH, true, false>(v, S, tx0, ty0, pg, t, c);
+  if (t + NT < m) load_group<TW, TH, true, false>(v, S, tx0, ty0, pg, t + NT, d);
+  if (t < n) put_group2<TW, TH, true, true>(rec, vb, t, t, a);
+  if (t + NT < n) put_group2<TW, TH, true, true>(rec, vb, t + NT, t + NT, b);
+  if (t < m) put_group2<TW, TH, true, false>(rec, vb, t, n + t, c);
+  if (t + NT < m) put_group2<TW, TH, true, false>(rec, vb, t + NT, n + t + NT, d);
+  for (int i = t + 2 * NT; i < n; i += NT) {
+    load_group<TW, TH, true, true>(v, S, tx0, ty0, 0, i, a);
+    if (i < m) load_group<TW, TH, true, false>(v, S, tx0, ty0, pg, i, c);
+    put_group2<TW, TH, true, true>(rec, vb, i, i, a);
+    if (i < m) put_group2<TW, TH, true, false>(rec, vb, i, n + i, c);
+  }
+}
+template <int TW, int TH>
+__device__ __forceinline__ void stage2_last(const ViewK &v, const SamplesK &S, float4 *rec, int tx0, int ty0, int pg) {
+  constexpr int NT = TW * TH, NG = Window<TW, TH>::NG;
+  const int t = threadIdx.x, n = (S.spp - pg) * NG;
+  RecordGroup a, b;
+  if (t < n) load_group<TW, TH, false, true>(v, S, tx0, ty0, pg, t, a);
+  if (t + NT < n) load_group<TW, TH, false, true>(v, S, tx0, ty0, pg, t + NT, b);
+  if (t < n) put_group2<TW, TH, false, true>(rec, nullptr, t, t, a);
+  if (t + NT < n) put_group2<TW, TH, false, true>(rec, nullptr, t + NT, t + NT, b);
+  for (int i = t + 2 * NT; i < n; i += NT) {
+    load_group<TW, TH, false, true>(v, S, tx0, ty0, pg, i, a);
+    put_group2<TW, TH, false, true>(rec, nullptr, i, i, a);
   }
 }
 
@@ -1136,11 +1199,11 @@ template <int TW, int TH>
 __device__ __forceinline__ int build_list2(const ParamsK &P, const uint32_t *vb, const int16_t *ptab,
                                            uint16_t *list, int col, int lx, int ly, int npick, int spp,
                                            uint32_t pix, int &n0) {
-  constexpr int SW = TW + 2 * kR, SH = TH + 2 * kR, SA = SW * SH, NT = TW * TH;
+  constexpr int SW = TW + 8, SA = em2_stride(TW, TH), NT = TW * TH;
   const int cap = spp + 20;
   const int split = em2_planes(spp) * SA;  // first record of the last pass
   const uint32_t cs = (uint32_t)(kCand * spp);
-  const int own = (ly + kR) * SW + (lx + kR);
+  const int own = (ly + kR) * SW + (lx + 4);
   int a = 0, b = 0;  // entries of the first and of the last pass
   auto put = [&](int e, bool ok) {
     const bool last = e >= split;
@@ -1178,13 +1241,11 @@ __device__ __forceinline__ int build_list2(const ParamsK &P, const uint32_t *vb,
 
 template <typename Op, int TW, int TH>
 __device__ __forceinline__ void em_tile2(const ParamsK &P, const ViewK &v, const SamplesK &S, const Op &op, int tx0,
-                                         int ty0, int rot, float4 *lds, EmShared<TW * TH> &sh,
-                                         const EmInput<TW, TH> &R) {
-  constexpr int SW = TW + 2 * kR, SH = TH + 2 * kR, SA = SW * SH, NT = TW * TH, IT = EmInput<TW, TH>::IT;
+                                         int ty0, int rot, float4 *lds, EmShared<TW * TH> &sh) {
+  constexpr int NT = TW * TH, SA = em2_stride(TW, TH);
   const int spp = S.spp, pg = em2_planes(spp), cap = spp + 20;
   float4 *rec = lds;
   uint32_t *vb = reinterpret_cast<uint32_t *>(lds + pg * SA);
-  const int nvb = (int)(em2_bits_bytes(TW, TH, spp) / 4);
   uint16_t *list = em_lists<TW, TH, true>(lds, spp);
   const int16_t *ptab = reinterpret_cast<const int16_t *>(list + cap * NT);
   uint8_t *work0 = reinterpret_cast<uint8_t *>(list + cap * NT) + pick_table_bytes(spp);
@@ -1194,22 +1255,10 @@ __device__ __forceinline__ void em_tile2(const ParamsK &P, const ViewK &v, const
   const int x0 = tx0 + t % TW, y0 = ty0 + t / TW;
   const bool in_image = x0 < v.W && y0 < v.H;
   if (t < 2 * kMaxLen) (&sh.cnt[0][0])[t] = 0;
-  for (int w = t; w < nvb; w += NT) vb[w] = 0u;
-  __syncthreads();  // the bits are zero before they are set
-  // plane 0 from the registers, then the other planes
-#pragma unroll
-  for (int i = 0; i < IT; ++i) {
-    const int e = t + i * NT;
-    if (IT * NT == SA || e < SA) {
-      const bool ok = R.st[i] == 1 && R.pp[i] > 0.0f;
-      rec[e] = ok ? make_float4(R.px[i], R.py[i], R.pz[i], R.pl[i] * frcp(fmaxf(R.pp[i], 1.17549435e-38f)))
-                  : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      if (ok) atomicOr(&vb[e >> 5], 1u << (e & 31));
-    }
-  }
-  stage2<TW, TH>(v, S, rec, vb, tx0, ty0, 1, spp, pg, true);
+  const EmPixel px0 = em_load_pixel(v, op, tx0, ty0, TW);
+  stage2_first<TW, TH>(v, S, rec, reinterpret_cast<uint8_t *>(vb), tx0, ty0, pg);
   int ncand = 0;
-  if (in_image && dot3(R.n, R.o) > 0.0f && R.rough >= P.rough_min) ncand = spp + n_picks(P, (int)R.k);
+  if (in_image && dot3(px0.n, px0.o) > 0.0f && px0.rough >= P.rough_min) ncand = spp + n_picks(P, (int)px0.k);
   sh.work[t] = (uint8_t)ncand;
   __syncthreads();
   int me;
@@ -1245,7 +1294,7 @@ __device__ __forceinline__ void em_tile2(const ParamsK &P, const ViewK &v, const
     for_each_record<2>(rec, list, NT, me, 0, 1, n0, [&](float4 r) { Op::visit(c, r, a); });
   }
   __syncthreads();  // the first planes' records are no longer read
-  stage2<TW, TH>(v, S, rec, vb, tx0, ty0, pg, spp, 0, false);
+  stage2_last<TW, TH>(v, S, rec, tx0, ty0, pg);
   __syncthreads();
   if (run) {
     const typename Op::Ctx c = Op::context(
@@ -1271,12 +1320,13 @@ __global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(TWO ? 5 
   const int tx0 = (tile % tiles_x) * TW, ty0 = (tile / tiles_x) * TH;
   build_em_pick_table<TW, TH, TWO>(lds, S.spp);  // before the loads: fewer live registers
   const EmOp<TG> op{gamma};
-  EmInput<TW, TH> R;
-  em_load(v, S, op, tx0, ty0, R);
-  if constexpr (TWO)
-    em_tile2(P, v, S, op, tx0, ty0, (int)blockIdx.x, lds, sh, R);
-  else
+  if constexpr (TWO) {
+    em_tile2<EmOp<TG>, TW, TH>(P, v, S, op, tx0, ty0, (int)blockIdx.x, lds, sh);
+  } else {
+    EmInput<TW, TH> R;
+    em_load(v, S, op, tx0, ty0, R);
     em_tile<EmOp<TG>, TW, TH, STALE, BATCH>(P, v, S, op, iterations, tx0, ty0, (int)blockIdx.x, lds, sh, R);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1387,12 +1437,13 @@ __global__ __launch_bounds__(TW *TH) void k_nll(ParamsK P, ViewK v, SamplesK S, 
   const int tile = xcd_tile(blockIdx.x, n_tiles);
   const int tx0 = (tile % tiles_x) * TW, ty0 = (tile / tiles_x) * TH;
   build_em_pick_table<TW, TH, TWO>(lds, S.spp);
-  EmInput<TW, TH> R;
-  em_load(v, S, op, tx0, ty0, R);
-  if constexpr (TWO)
-    em_tile2(P, v, S, op, tx0, ty0, (int)blockIdx.x, lds, sh, R);
-  else
+  if constexpr (TWO) {
+    em_tile2<NllOp<LOSS, GRAD>, TW, TH>(P, v, S, op, tx0, ty0, (int)blockIdx.x, lds, sh);
+  } else {
+    EmInput<TW, TH> R;
+    em_load(v, S, op, tx0, ty0, R);
     em_tile(P, v, S, op, 1, tx0, ty0, (int)blockIdx.x, lds, sh, R);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1509,12 +1560,13 @@ __global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(TH == 2 
   const ParamsK P = batch_params(hd->base, bv);
   build_em_pick_table<TW, TH, TWO>(lds, bv.S.spp);
   const EmOp<TG> op{(TG *)bv.gout};
-  EmInput<TW, TH> R;
-  em_load(bv.cur, bv.S, op, tx0, ty0, R);
-  if constexpr (TWO)
-    em_tile2(P, bv.cur, bv.S, op, tx0, ty0, (int)blockIdx.x, lds, sh, R);
-  else
+  if constexpr (TWO) {
+    em_tile2<EmOp<TG>, TW, TH>(P, bv.cur, bv.S, op, tx0, ty0, (int)blockIdx.x, lds, sh);
+  } else {
+    EmInput<TW, TH> R;
+    em_load(bv.cur, bv.S, op, tx0, ty0, R);
     em_tile(P, bv.cur, bv.S, op, 1, tx0, ty0, (int)blockIdx.x, lds, sh, R);
+  }
 }
 
 // Philox words for given counters (diagnostic entry).

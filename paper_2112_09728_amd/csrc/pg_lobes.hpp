@@ -43,13 +43,13 @@ __device__ __forceinline__ void lobes_reset(const ParamsK &P, float g[6 * K + 2]
 template <int K>
 __device__ __forceinline__ void lobes_load(const float *__restrict__ g, int plane, int idx, float out[6 * K + 2]) {
 #pragma unroll
-  for (int c = 0; c < 6 * K + 2; ++c) out[c] = g[c * plane + idx];
+  for (int c = 0; c < 6 * K + 2; ++c) out[c] = at(g + c * plane, idx);
 }
 
 template <int K>
 __device__ __forceinline__ void lobes_store(float *__restrict__ g, int plane, int idx, const float in[6 * K + 2]) {
 #pragma unroll
-  for (int c = 0; c < 6 * K + 2; ++c) g[c * plane + idx] = in[c];
+  for (int c = 0; c < 6 * K + 2; ++c) at(g + c * plane, idx) = in[c];
 }
 
 // Reprojection of one pixel (Sec. 3.1 with K lobes): the tests and the
@@ -66,12 +66,12 @@ __device__ __forceinline__ void lobes_reproject(const ParamsK &P, const ViewK &c
   float zp = 0.0f, mx = 0.0f, my = 0.0f;
   bool keep = has_prev && guided;
   if (keep) {
-    zp = cur.z[idx];
+    zp = at(cur.z, idx);
     if (cur.mv) {
-      mx = cur.mv[idx];
-      my = cur.mv[plane + idx];
+      mx = at(cur.mv, idx);
+      my = at(cur.mv + plane, idx);
     }
-    if (cur.mask != nullptr && cur.mask[idx] != 0) keep = false;
+    if (cur.mask != nullptr && at(cur.mask, idx) != 0) keep = false;
   }
   int qx = 0, qy = 0;
   if (keep) {
@@ -87,7 +87,7 @@ __device__ __forceinline__ void lobes_reproject(const ParamsK &P, const ViewK &c
   if (keep) {
     const int pplane = prev.H * prev.pitch;
     const int qidx = qy * prev.pitch + qx;
-    const float zq = prev.z[qidx];
+    const float zq = at(prev.z, qidx);
     const V3 nq = load3(prev.n, pplane, qidx);
     lobes_load<K>(gprev, pplane, qidx, g);
     if (fabsf(zp - zq) > P.tau_z * zp) keep = false;
@@ -202,12 +202,12 @@ __device__ __forceinline__ void lobes_sample(const ParamsK &P, const ViewK &v, c
       D = 0.0f;
       pb = 0.0f;
     }
-    S.dir[rec] = wd.x;
-    S.dir[splane + rec] = wd.y;
-    S.dir[2 * splane + rec] = wd.z;
-    S.pmix[rec] = D;
-    S.pb[rec] = pb;
-    S.strat[rec] = code;
+    at(S.dir, rec) = wd.x;
+    at(S.dir + splane, rec) = wd.y;
+    at(S.dir + 2 * splane, rec) = wd.z;
+    at(S.pmix, rec) = D;
+    at(S.pb, rec) = pb;
+    at(S.strat, rec) = code;
   }
 }
 
@@ -246,7 +246,7 @@ __global__ __launch_bounds__(256) void k_lobes_pdf(ParamsK P, ViewK v, const flo
   for (int j = 0; j < K; ++j) tot += guided ? g[6 * j + 5] : 0.0f;
   for (int s = 0; s < n_per_px; ++s) {
     const int r = (s * v.H + y) * v.pitch + x;
-    const V3 w = V3{dir[r], dir[dplane + r], dir[2 * dplane + r]};
+    const V3 w = load3(dir, dplane, r);
     float D = 0.0f;
     if (valid && dot3(w, w) > 0.0f) {
       const V3 l = to_local(px.f, normalized(w));
@@ -263,7 +263,7 @@ __global__ __launch_bounds__(256) void k_lobes_pdf(ParamsK P, ViewK v, const flo
         }
       }
     }
-    pmix[r] = D;
+    at(pmix, r) = D;
   }
 }
 
@@ -354,7 +354,10 @@ __device__ __forceinline__ void stage_records_vpl(const ViewK &v, const SamplesK
     in[i] = e < SA && gx >= 0 && gy >= 0 && gx < v.W && gy < v.H;
     gi[i] = gy * v.pitch + gx;
     xq[i] = V3{0.0f, 0.0f, 0.0f};
-    if (in[i]) xq[i] = V3{pos[gi[i]] - cref.x, pos[plane + gi[i]] - cref.y, pos[2 * plane + gi[i]] - cref.z};
+    if (in[i]) {
+      const V3 x = load3(pos, plane, gi[i]);
+      xq[i] = V3{x.x - cref.x, x.y - cref.y, x.z - cref.z};
+    }
   }
   for (int s = 0; s < S.spp; ++s) {
     uint8_t st[IT];
@@ -508,7 +511,7 @@ __global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(K == 2 &
       const int idx0 = y0 * v.pitch + x0;
       const PixelIn pin = load_pixel(v, idx0);
       if (dot3(pin.n, pin.o) > 0.0f && pin.rough >= P.rough_min)
-        ncand = spp + n_picks(P, (int)gamma[(6 * K + 1) * plane + idx0]);
+        ncand = spp + n_picks(P, (int)at(gamma + (6 * K + 1) * plane, idx0));
     }
   }
   V3 cref = V3{0.0f, 0.0f, 0.0f};
@@ -517,7 +520,10 @@ __global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(K == 2 &
     cref = load3(pos, plane, ci);
     stage_records_vpl<TW, TH>(v, S, pos, hit, cref, lds, tx0, ty0);
   } else {
-    stage_records<TW, TH>(v, S, lds, tx0, ty0, 0);
+    if (few_records(v, S))
+      stage_few<TW, TH>(v, S, lds, tx0, ty0);
+    else
+      stage_records<TW, TH>(v, S, lds, tx0, ty0, 0);
   }
   sh.work[t] = (uint8_t)ncand;
   __syncthreads();
@@ -540,7 +546,10 @@ __global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(K == 2 &
     const int idx = (ty0 + me / TW) * v.pitch + tx0 + me % TW;
     lobes_load<K>(gamma, plane, idx, g);
     V3 xp = V3{0.0f, 0.0f, 0.0f};
-    if (VPL) xp = V3{pos[idx] - cref.x, pos[plane + idx] - cref.y, pos[2 * plane + idx] - cref.z};
+    if (VPL) {
+      const V3 x = load3(pos, plane, idx);
+      xp = V3{x.x - cref.x, x.y - cref.y, x.z - cref.z};
+    }
     lobes_update<K, VPL>(P, v, idx, lds, list + me, NT, len, g, xp);
   }
   // write-back in natural order through LDS (full cache lines), over the
@@ -556,7 +565,7 @@ __global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(K == 2 &
   if (sh.work[t] > 0 && x0 < v.W && y0 < v.H) {
     const int idx0 = y0 * v.pitch + x0;
 #pragma unroll
-    for (int c = 0; c < 6 * K + 2; ++c) gamma[c * plane + idx0] = wb[c * NT + t];
+    for (int c = 0; c < 6 * K + 2; ++c) at(gamma + c * plane, idx0) = wb[c * NT + t];
   }
 }
 
@@ -598,10 +607,10 @@ __global__ __launch_bounds__(256) void k_light_ceiling(CeilingK C, ViewK v, cons
   const V3 xp = load3(pos, plane, idx);
   for (int s = 0; s < S.spp; ++s) {
     const int r = (s * v.H + y) * v.pitch + x;
-    const uint8_t code = S.strat[r];
+    const uint8_t code = at(S.strat, r);
     float L = 0.0f, t = 0.0f;
     if (code == 1 || code == 2) {
-      const V3 w = normalized(V3{S.dir[r], S.dir[splane + r], S.dir[2 * splane + r]});
+      const V3 w = normalized(load3(S.dir, splane, r));
       if (w.z > 0.0f) {
         t = (C.z - xp.z) / w.z;
         L = ceiling_emission(C, fmaf(t, w.x, xp.x), fmaf(t, w.y, xp.y));
@@ -610,8 +619,8 @@ __global__ __launch_bounds__(256) void k_light_ceiling(CeilingK C, ViewK v, cons
         L = C.ambient;
       }
     }
-    S.L[r] = L;
-    hit[r] = t;
+    at(S.L, r) = L;
+    at(hit, r) = t;
   }
 }
 

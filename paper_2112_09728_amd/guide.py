@@ -31,7 +31,8 @@ def _tile_lds(tile, spp: int) -> int:
     lists = (spp + 20) * w * h * 2 + ((48 * spp * 2 + 15) & ~15)
     if spp < 4:
         return sa * spp * 16 + lists
-    bits = ((spp * sa + 31) // 32 * 4 + 15) & ~15
+    sa = (w + 8) * (h + 6)
+    bits = (spp * sa // 8 + 15) & ~15
     return sa * ((spp + 1) // 2) * 16 + bits + lists + w * h
 
 
