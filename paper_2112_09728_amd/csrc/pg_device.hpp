@@ -72,6 +72,9 @@ struct __attribute__((packed, aligned(1))) Byte4U {
 __device__ __forceinline__ F4 load4(const float *p, int i) {
   return *reinterpret_cast<const F4U *>(reinterpret_cast<const char *>(p) + (uint32_t)i * 4u);
 }
+__device__ __forceinline__ void store4(float *p, int i, F4 v) {
+  *reinterpret_cast<F4U *>(reinterpret_cast<char *>(p) + (uint32_t)i * 4u) = v;
+}
 __device__ __forceinline__ uint32_t load4(const uint8_t *p, int i) {
   return reinterpret_cast<const Byte4U *>(p + (uint32_t)i)->v;
 }

@@ -564,7 +564,8 @@ pg_status pg_light_field(const pg_lights *lights, const pg_view *v, const uint8_
   const LightsK L = to_k(lights);
   const ViewK V = to_k(v);
   const SamplesK S = to_k(samples);
-  hipLaunchKernelGGL(k_light, stream_grid(V.W, V.H), dim3(64, 4), 0, (hipStream_t)stream, L, V, vis, S);
+  hipLaunchKernelGGL(k_light, dim3(((V.W + 127) / 128) * ((V.H + 7) / 8), S.spp), dim3(32, 8), 0, (hipStream_t)stream, L,
+                     V, vis, S);
   return check_launch("pg_light_field");
 }
 
