@@ -214,25 +214,28 @@ __device__ __forceinline__ float atan_4pi_unit(float t) {
 // avoids the cancellation of 1 - w_z; inside each of the four concentric
 // sectors the disk angle is atan of the ratio of the smaller to the larger of
 // w_x, w_y (the disk scaling cancels in that ratio).  Branch free.
-// hemi2sq_c gives the point o = 2u - 1 of the centred square, hemi2sq the
-// point u of the unit square.
-__device__ __forceinline__ void hemi2sq_c(V3 w, float &ox, float &oy) {
+// hemi2sq_c gives the point c = u - 1/2, hemi2sq the point u of the unit
+// square.  (rho / 2 comes out of the reciprocal square root for a factor 4 of
+// its argument, exactly; the floors keep 0 * inf from the pole w = (0, 0, 1),
+// and act on no other argument.)
+__device__ __forceinline__ void hemi2sq_c(V3 w, float &cx, float &cy) {
+  constexpr float kTiny = 1.17549435e-38f;
   const float s2 = fmaf(w.x, w.x, w.y * w.y);
-  const float rho = s2 > 0.0f ? s2 * __builtin_amdgcn_rsqf(s2 * (1.0f + w.z)) : 0.0f;
+  const float rho = s2 * __builtin_amdgcn_rsqf(fmaxf(s2 * fmaf(4.0f, w.z, 4.0f), kTiny));
   const bool bigx = fabsf(w.x) > fabsf(w.y);
   const float num = bigx ? w.y : w.x;
   const float den = bigx ? w.x : w.y;
-  const float t = den != 0.0f ? num * __builtin_amdgcn_rcpf(den) : 0.0f;
+  const float t = num * __builtin_amdgcn_rcpf(fmaxf(fabsf(den), kTiny));
   const float r = copysignf(rho, den);
-  const float o = r * atan_4pi_unit(t);
-  ox = bigx ? r : o;
-  oy = bigx ? o : r;
+  const float o = rho * atan_4pi_unit(t);
+  cx = bigx ? r : o;
+  cy = bigx ? o : r;
 }
 __device__ __forceinline__ void hemi2sq(V3 w, float &ux, float &uy) {
-  float ox, oy;
-  hemi2sq_c(w, ox, oy);
-  ux = fmaf(0.5f, ox, 0.5f);
-  uy = fmaf(0.5f, oy, 0.5f);
+  float cx, cy;
+  hemi2sq_c(w, cx, cy);
+  ux = cx + 0.5f;
+  uy = cy + 0.5f;
 }
 // ---------------------------------------------------------------------------
 // Synthetic material: Lambert + GGX (Walter et al., EGSR 2007) with Smith G1
@@ -265,8 +268,9 @@ __device__ __forceinline__ float smith_g1(V3 v, float alpha2) {
 // (1 - s_d) / (4 pi).
 __device__ __forceinline__ void brdf_eval(const Pixel &px, V3 wi, float &f, float &pdf) {
   const V3 h = V3{px.wo.x + wi.x, px.wo.y + wi.y, px.wo.z + wi.z};
-  const float hh = dot3(h, h);
-  const float den = fmaf(px.alpha2, h.z * h.z, fmaf(h.x, h.x, h.y * h.y));
+  const float hxy = fmaf(h.x, h.x, h.y * h.y);
+  const float hh = fmaf(h.z, h.z, hxy);
+  const float den = fmaf(px.alpha2, h.z * h.z, hxy);
   const float q = fsqrt(fmaf(px.alpha2, fmaf(wi.x, wi.x, wi.y * wi.y), wi.z * wi.z));
   const float wq = wi.z + q;
   const float woh_u = dot3(px.wo, h);  // |h| (wo . h_hat)
@@ -322,7 +326,7 @@ __device__ __forceinline__ float gauss_q(const Gauss &g, float ux, float uy) {
 
 // The weighted Gaussian term pi N(u) / (2 pi) of a lobe as the E-step
 // evaluates it, at a point given relative to the lobe's mean, r = u - mu =
-// o/2 + h with h = 1/2 - mu, formed from the centred point o in one rounding
+// c + h with h = 1/2 - mu, formed from the centred point c in one rounding
 // (h is exact for mu >= 1/4, within half an ulp of 1/2 below; the mean is
 // added back as 1/2 - h, exactly the centre the points were measured from):
 //   pi_norm exp2(-log2(e)/2 (z1^2 + z2^2)),  z1 = i11 rx,  z2 = i22 ry + c21 z1,

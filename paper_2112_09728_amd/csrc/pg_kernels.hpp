@@ -682,9 +682,9 @@ struct EmCtx {
 __device__ __forceinline__ void em_visit(const EmCtx &c, float4 r, Accum &a) {
   const V3 l = to_local(c.px.f, V3{r.x, r.y, r.z});
   if (l.z <= 0.0f) return;
-  float ox, oy, f, pb;
-  hemi2sq_c(l, ox, oy);
-  const float rx = fmaf(0.5f, ox, c.T.hx), ry = fmaf(0.5f, oy, c.T.hy);
+  float cx, cy, f, pb;
+  hemi2sq_c(l, cx, cy);
+  const float rx = cx + c.T.hx, ry = cy + c.T.hy;
   brdf_eval(c.px, l, f, pb);
   const float w = r.w * f * l.z;
   const float ga = lobe_eval(c.T, rx, ry);
@@ -1410,9 +1410,9 @@ struct NllOp {
     if (r.w == 0.0f) return;
     const V3 l = to_local(c.px.f, V3{r.x, r.y, r.z});
     if (l.z <= 0.0f) return;
-    float ox, oy, f, pb;
-    hemi2sq_c(l, ox, oy);
-    const float rx = fmaf(0.5f, ox, c.T.hx), ry = fmaf(0.5f, oy, c.T.hy);
+    float cx, cy, f, pb;
+    hemi2sq_c(l, cx, cy);
+    const float rx = cx + c.T.hx, ry = cy + c.T.hy;
     brdf_eval(c.px, l, f, pb);
     const float w = r.w * f * l.z;
     const float z1 = rx * c.T.i11;
