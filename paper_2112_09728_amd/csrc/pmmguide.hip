@@ -168,15 +168,17 @@ struct Tile {
 constexpr Tile kTiles[] = {{32, 8}, {16, 16}, {64, 4}, {32, 4}, {16, 8}, {64, 2}, {32, 16}, {64, 8}};
 
 // Default training tile per spp (1080p pan, EM per frame).  The two-pass
-// tile (online EM from spp 4) runs best at 16x16 (spp 4 230 us against 239
-// at 32x8; spp 6 295 against 356; spp 8 382 against 401 and 437 at 16x8).
+// tile (online EM from spp 4) runs best at 16x16 up to spp 6 (spp 4 201 us
+// against 216 at 32x8, spp 5 235 against 272, spp 6 250 against 289: 16x16
+// holds one block more per CU) and at 32x8 above (spp 7 317 against 328, spp 8
+// 336 against 343: 3 blocks per CU either way).
 // The single-pass tile (up to spp 3, and batch EM or the stale test above):
 // 32x8 up to spp 4; above, the staged records limit how many blocks share a
 // CU's LDS, and the shape that keeps the most waves resident wins: 16x16 at
 // spp 5 (266 us against 339 for 32x4), 16x8 at spp 6-8 (spp 8: 508 us
 // against 726).
 Tile default_tile(int spp, bool two) {
-  if (two) return Tile{16, 16};
+  if (two) return spp <= 6 ? Tile{16, 16} : Tile{32, 8};
   return spp <= 4 ? Tile{32, 8} : (spp == 5 ? Tile{16, 16} : Tile{16, 8});
 }
 
