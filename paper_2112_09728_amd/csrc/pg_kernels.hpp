@@ -226,14 +226,15 @@ struct LightsK {
   float l[8][5];
 };
 
-// exp(x) for x <= 0 to about 1.5 ulp: the hardware exp2 of the rounded product
-// x log2(e), corrected by the product's rounding error (first order).  Below
-// 2^-126 it gives 0.
-__device__ __forceinline__ float exp_neg(float x) {
+// exp(x) to about 1.5 ulp: the hardware exp2 of the rounded product x log2(e),
+// corrected by the product's rounding error (first order).  Below 2^-126 it
+// gives 0.  (The clamps act only where the product or the result is infinite,
+// and keep inf - inf and 0 * inf out of the correction.)
+__device__ __forceinline__ float exp_fast(float x) {
   const float t = x * 1.44269504088896340736f;
   const float lo = fmaf(x, 1.92596299e-8f, fmaf(x, 1.44269504088896340736f, -t));
   const float e = __builtin_amdgcn_exp2f(t);
-  return fmaf(e * 0.693147180559945309417f, lo, e);
+  return fmaf(fminf(e, 3.40282347e38f) * 0.693147180559945309417f, __builtin_amdgcn_fmed3f(lo, -1.0f, 1.0f), e);
 }
 
 __device__ __forceinline__ float light_radiance(const LightsK &Lt, uint32_t bits, V3 wdir) {
@@ -243,7 +244,7 @@ __device__ __forceinline__ float light_radiance(const LightsK &Lt, uint32_t bits
     const V3 a = V3{w.x - Lt.l[k][0], w.y - Lt.l[k][1], w.z - Lt.l[k][2]};
     // (every light is evaluated: with a bit per pixel and light hardly any
     // wave could skip one)
-    const float with = fmaf(Lt.l[k][4], exp_neg(-0.5f * Lt.l[k][3] * dot3(a, a)), L);
+    const float with = fmaf(Lt.l[k][4], exp_fast(-0.5f * Lt.l[k][3] * dot3(a, a)), L);
     L = ((bits >> k) & 1u) ? with : L;
   }
   return L;

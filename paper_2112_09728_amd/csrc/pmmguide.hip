@@ -740,8 +740,16 @@ pg_status pg_light_ceiling(const pg_ceiling *c, const pg_view *v, const float *p
   C.lamps = c->lamps;
   const ViewK V = to_k(v);
   const SamplesK S = to_k(samples);
-  hipLaunchKernelGGL(k_light_ceiling, stream_grid(V.W, V.H), dim3(64, 4), 0, (hipStream_t)stream, C, V, position, S,
-                     hit_dist);
+  // the lamp table in LDS up to 32 KiB (5 blocks a CU), read by as many blocks
+  // as that keeps resident on 256 CUs
+  const int n = (int)stream_grid(V.W, V.H).x;
+  const int64_t cells = ((int64_t)C.nx + 4) * ((int64_t)C.ny + 4);
+  if (cells * 16 <= 32 * 1024)
+    hipLaunchKernelGGL((k_light_ceiling<true>), dim3(n < 1280 ? n : 1280), dim3(256), (size_t)cells * 16,
+                       (hipStream_t)stream, C, V, position, S, hit_dist, n);
+  else
+    hipLaunchKernelGGL((k_light_ceiling<false>), dim3(n), dim3(256), 0, (hipStream_t)stream, C, V, position, S, hit_dist,
+                       n);
   return check_launch("pg_light_ceiling");
 }
 

@@ -1,0 +1,64 @@
+"""The two radiance stand-ins at the edges of their kernels: rows that are no
+multiple of the light field's four pixels a lane, the exponential's extremes,
+and the ceiling's lamp table in LDS against the lattice read from memory."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import paper_2112_09728_amd as pg
+from paper_2112_09728_amd import workload as wl
+from pgtest import dev, gpu_view, host
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+
+
+def _samples(H, W, spp, rng):
+    """Unit directions and every strategy code."""
+    d = rng.normal(size=(3, spp, H, W))
+    d = (d / np.linalg.norm(d, axis=0)).astype(np.float32)
+    code = rng.integers(0, 5, (spp, H, W)).astype(np.uint8)
+    z = np.zeros((spp, H, W), np.float32)
+    return d, code, pg.Samples.wrap(dev(d), dev(z), dev(z), dev(code), dev(z + 7))
+
+
+@pytest.mark.parametrize("W,H,spp", [(1, 1, 1), (2, 3, 2), (3, 1, 8), (5, 9, 3), (127, 8, 1), (129, 7, 2), (260, 17, 1)])
+def test_light_field_rows_and_extremes(W, H, spp):
+    rng = np.random.default_rng(100 * W + spp)
+    scene = wl.make_scene(W, H, 5)
+    # an ordinary light, one without falloff, ones so sharp that only 0 is left
+    # (finite and infinite), and one that grows away from its axis
+    lights = np.array([[0.6, 0.0, 0.8, 30, 4], [0, 0, 1, 0, 2], [0, 1, 0, 1e30, 9], [0, 0.8, 0.6, 3e38, 9],
+                       [1, 0, 0, -3, 0.5]], np.float32)
+    vis = rng.integers(0, 32, (H, W)).astype(np.uint8)
+    d, code, s = _samples(H, W, spp, rng)
+    pg.light_field(pg.lights_struct(lights, 0.05), gpu_view(scene), dev(vis), s)
+    torch.cuda.synchronize()
+    got = host(s.radiance)
+    want = O.light(lights.astype(np.float64), 0.05, vis, d, code)
+    # exp's argument x carries sqrt(2 x lambda) 2^-23 of the direction's
+    # rounding (x <= 88 wherever the term is not 0): below 1e-5 at lambda 30
+    assert (np.abs(got - want) <= 2e-5 * np.abs(want)).all()
+    assert (got[(code != 1) & (code != 2)] == 0).all()
+
+
+@pytest.mark.parametrize("W,H,spp", [(1, 1, 1), (66, 5, 2), (130, 33, 1)])
+def test_ceiling_table_and_memory_lattice_agree(W, H, spp):
+    rng = np.random.default_rng(W + spp)
+    scene = wl.make_scene(W, H, 6)
+    d, _, s = _samples(H, W, spp, rng)
+    nx, ny = 4, 3
+    lamps = np.stack([rng.uniform(-40, 150, (ny, nx)), rng.uniform(-40, 110, (ny, nx)), rng.uniform(3, 8, (ny, nx)),
+                      rng.uniform(2, 30, (ny, nx))], -1).astype(np.float32)
+    big = np.zeros((60, 60, 4), np.float32)  # the same lamps among dark cells: no room in LDS
+    big[..., 2] = 1.0
+    big[:ny, :nx] = lamps
+    out = []
+    for t in (lamps, big):
+        c = pg.Ceiling(dict(z=32.0, period=48.0, x0=-48.0, y0=-48.0, ambient=0.05, lamps=t))
+        hit = torch.empty((spp, H, W), device="cuda")
+        pg.light_ceiling(c, gpu_view(scene), dev(scene["position"]), s, hit)
+        torch.cuda.synchronize()
+        out.append((host(s.radiance).copy(), host(hit)))
+    assert (out[0][0] == out[1][0]).all() and (out[0][1] == out[1][1]).all()
