@@ -725,23 +725,24 @@ __device__ __forceinline__ void em_visit(const EmCtx &c, float4 r, Accum &a) {
   }
 }
 
-// Bytes of the pick table in dynamic LDS (after the records and the lists).
+// Pick table of a tile shape (records in rows of SW, planes of SA), after the
+// lists in dynamic LDS: code c in [0, 48 spp) of a pick, (o, s) = (c div spp,
+// c mod spp), the centre of the window skipped and (dx, dy) = (o mod 7 - 3, o
+// div 7 - 3), to the offset s SA + dy SW + dx of its candidate from the
+// pixel's own record of plane 0, so that a pick costs one LDS read and one
+// addition.  Built once per block.
 __host__ __device__ constexpr int pick_table_bytes(int spp) { return (kCand * spp * 2 + 15) & ~15; }
 
-// Pick table of a tile shape: code c in [0, 48 spp) of a pick -> offset of
-// its candidate's staged record from the pixel's own: s SA + dy SW + dx with
-// (o, s) = (c div spp, c mod spp), the centre of the window skipped, and
-// (dx, dy) = (o mod 7 - 3, o div 7 - 3).  Built once per block, so that a
-// pick costs one LDS read instead of integer arithmetic.
 template <int SA, int SW>
 __device__ __forceinline__ void build_pick_table(int16_t *tab, int spp) {
   // c div spp = (c ceil(2^16 / spp)) >> 16, exact for c < 48 spp
   const uint32_t inv_spp = (65536u + (uint32_t)spp - 1u) / (uint32_t)spp;
   for (int c = (int)threadIdx.x; c < kCand * spp; c += (int)blockDim.x) {
-    const int o0 = (int)(__umul24((uint32_t)c, inv_spp) >> 16), s = c - o0 * spp;
-    const int o = o0 + (o0 >= kCand / 2 ? 1 : 0);
-    const int row = o / kSide;
-    tab[c] = (int16_t)(s * SA + (row - kR) * SW + (o - row * kSide - kR));
+    const uint32_t o0 = __umul24((uint32_t)c, inv_spp) >> 16;
+    const int s = c - (int)__umul24(o0, (uint32_t)spp);
+    const uint32_t o = o0 + (o0 >= (uint32_t)(kCand / 2) ? 1u : 0u);
+    const uint32_t row = __umul24(o, 37u) >> 8;  // o / 7, exact for o < 49
+    tab[c] = (int16_t)(s * SA + (int)(o + __umul24(row, (uint32_t)(SW - kSide))) - (kR * SW + kR));
   }
 }
 
@@ -782,9 +783,16 @@ __device__ __forceinline__ void build_em_pick_table(float4 *lds, int spp) {
 }
 
 // Number of neighbour picks N(k) = 5 + floor(15 (kMax - k) / kMax) (Sec. 4.2).
+// The quotient is at most 15, so the product with the reciprocal is off by at
+// most one, which the remainder shows (an integer division is 25
+// instructions).
 __device__ __forceinline__ int n_picks(const ParamsK &P, int k) {
-  k = k < 0 ? 0 : (k > P.k_max ? P.k_max : k);
-  return 5 + (15 * (P.k_max - k)) / P.k_max;
+  k = min(max(k, 0), P.k_max);
+  const int a = 15 * (P.k_max - k);
+  int q = (int)((float)a * frcp((float)P.k_max));
+  const int r = a - q * P.k_max;
+  q += (r >= P.k_max ? 1 : 0) - (r < 0 ? 1 : 0);
+  return 5 + q;
 }
 
 // A list entry is the byte offset of its staged record from the start of the
@@ -1101,7 +1109,7 @@ __device__ __forceinline__ void em_tile(const ParamsK &P, const ViewK &v, const 
   const int t = threadIdx.x;
   const int x0 = tx0 + t % TW, y0 = ty0 + t / TW;
   const bool in_image = x0 < v.W && y0 < v.H;
-  int16_t *ptab = reinterpret_cast<int16_t *>(list + (S.spp + 20) * NT);
+  const int16_t *ptab = reinterpret_cast<const int16_t *>(list + (S.spp + 20) * NT);
   if (t < 2 * kMaxLen) (&sh.cnt[0][0])[t] = 0;
   if (few_records(v, S)) {
     stage_few<TW, TH>(v, S, lds, tx0, ty0);
@@ -1250,23 +1258,24 @@ __device__ __forceinline__ int build_list2(const ParamsK &P, const uint32_t *vb,
                                            uint16_t *list, int col, int lx, int ly, int npick, int spp,
                                            uint32_t pix, int &n0) {
   constexpr int SW = TW + 8, SA = em2_stride(TW, TH), NT = TW * TH;
-  const int cap = spp + 20;
-  const int split = em2_planes(spp) * SA;  // first record of the last pass
+  const int cap = spp + 20, pg = em2_planes(spp), split = pg * SA;  // the first record of the last pass
   const uint32_t cs = (uint32_t)(kCand * spp);
   const int own = (ly + kR) * SW + (lx + 4);
-  int a = 0, b = 0;  // entries of the first and of the last pass
-  auto put = [&](int e, bool ok) {
-    const bool last = e >= split;
-    const int slot = last ? cap - 1 - b : a;  // a rejected entry is overwritten by the next
-    list[slot * NT + col] = (uint16_t)((last ? e - split : e) << 4);
-    a += (ok && !last) ? 1 : 0;
-    b += (ok && last) ? 1 : 0;
-  };
+  // where the next entry of the first and of the last pass goes
+  char *const a0 = reinterpret_cast<char *>(list + col), *const b0 = a0 + (cap - 1) * 2 * NT;
+  char *a = a0, *b = b0;
 #pragma unroll
   for (int s = 0; s < kMaxSpp; ++s)
     if (s < spp) {
       const int e = s * SA + own;
-      put(e, (vb[e >> 5] >> (e & 31)) & 1u);
+      const int step = (int)((vb[e >> 5] >> (e & 31)) & 1u) * (2 * NT);
+      if (s < pg) {  // (a rejected entry is overwritten by the next)
+        *reinterpret_cast<uint16_t *>(a) = (uint16_t)(e << 4);
+        a += step;
+      } else {
+        *reinterpret_cast<uint16_t *>(b) = (uint16_t)((e - split) << 4);
+        b -= step;
+      }
     }
   for (int m0 = 0; m0 < npick; m0 += 8) {
     const uint4 w4 = philox4x32_10(pix, P.frame, (1u << 16) | (uint32_t)(m0 >> 3), P.view, P.key0, P.key1);
@@ -1280,13 +1289,19 @@ __device__ __forceinline__ int build_list2(const ParamsK &P, const uint32_t *vb,
       e[j] = own + ptab[__umul24(h, cs) >> 16];
     }
 #pragma unroll
-    for (int j = 0; j < 8; ++j) wv[j] = vb[e[j] >> 5];
+    for (int j = 0; j < 8; ++j) wv[j] = vb[e[j] >> 5] >> (e[j] & 31);
 #pragma unroll
     for (int j = 0; j < 8; ++j)
-      if (m0 + j < npick) put(e[j], (wv[j] >> (e[j] & 31)) & 1u);
+      if (m0 + j < npick) {
+        const bool last = e[j] >= split;
+        *reinterpret_cast<uint16_t *>(last ? b : a) = (uint16_t)((e[j] - (last ? split : 0)) << 4);
+        const int step = (int)(wv[j] & 1u) * (2 * NT), back = last ? step : 0;
+        a += step - back;
+        b -= back;
+      }
   }
-  n0 = a;
-  return a + b;
+  n0 = (int)((uint32_t)(a - a0) / (2u * NT));
+  return n0 + (int)((uint32_t)(b0 - b) / (2u * NT));
 }
 
 template <typename Op, int TW, int TH>
