@@ -457,22 +457,25 @@ __global__ __launch_bounds__(256) void k_pdf(ParamsK P, ViewK v, const TG *__res
 }
 
 
-// The light field over the records of one sample plane per blockIdx.y, four
-// pixels of a row a lane in blocks of 32x8 lanes (128x8 pixels): 16-byte loads
-// and stores, and four independent chains of arithmetic to cover them.  Bound
-// by HBM: 17 B a record and 1 B a pixel.  One pixel a lane and all of its
+// The light field over the records of one sample plane per blockIdx.y.  FOUR:
+// four pixels of a row a lane in blocks of 32x8 lanes (128x8 pixels): 16-byte
+// loads and stores, and four independent chains of arithmetic to cover them.
+// Bound by HBM: 17 B a record and 1 B a pixel.  One pixel a lane and all of its
 // samples in turn took 66.0 us at 1080p and 8 spp (now 44.6: 6.4 TB/s, part of
-// it from the Infinity Cache) and 33.8 us at 4K and 1 spp (now 23.2); at 64x64
-// the two forms do not differ.
+// it from the Infinity Cache) and 33.8 us at 4K and 1 spp (now 23.2).  Without
+// FOUR one pixel a lane (64x4), a quarter of the work in each: the shorter
+// chain where the lanes do not fill the chip anyway.
+template <bool FOUR>
 __global__ __launch_bounds__(256) void k_light(LightsK Lt, ViewK v, const uint8_t *__restrict__ vis,
                                                SamplesK S) {
   const int plane = v.H * v.pitch, splane = S.spp * plane, s = (int)blockIdx.y;
-  const int tx = (v.W + 127) >> 7, n = tx * ((v.H + 7) >> 3);
+  constexpr int BW = FOUR ? 128 : 64, BH = FOUR ? 8 : 4;
+  const int tx = (v.W + BW - 1) / BW, n = tx * ((v.H + BH - 1) / BH);
   const int t = xcd_tile((int)blockIdx.x, n);
-  const int x = (t % tx) * 128 + 4 * (int)threadIdx.x, y = (t / tx) * 8 + (int)threadIdx.y;
+  const int x = (t % tx) * BW + (FOUR ? 4 : 1) * (int)threadIdx.x, y = (t / tx) * BH + (int)threadIdx.y;
   if (x >= v.W || y >= v.H) return;
   const int idx = row_off(y, v.pitch) + x, r = s * plane + idx;
-  if (x + 4 <= v.W) {
+  if (FOUR && x + 4 <= v.W) {
     const uint32_t bits = vis ? load4(vis, idx) : 0u, st = load4(S.strat, r);
     const F4 dx = load4(S.dir, r), dy = load4(S.dir + splane, r), dz = load4(S.dir + 2 * splane, r);
     F4 L;
@@ -485,11 +488,11 @@ __global__ __launch_bounds__(256) void k_light(LightsK Lt, ViewK v, const uint8_
     store4(S.L, r, L);
     return;
   }
-  for (int j = 0; x + j < v.W; ++j) {  // the end of a row
+  for (int j = 0; FOUR ? x + j < v.W : j < 1; ++j) {  // the end of a row, or the lane's one pixel
     const uint8_t code = at(S.strat, r + j);
-    at(S.L, r + j) = code == 1 || code == 2
-                         ? light_radiance(Lt, vis ? at(vis, idx + j) : 0u, load3(S.dir, splane, r + j))
-                         : 0.0f;
+    const uint32_t bits = vis ? at(vis, idx + j) : 0u;
+    const V3 w = load3(S.dir, splane, r + j);
+    at(S.L, r + j) = code == 1 || code == 2 ? light_radiance(Lt, bits, w) : 0.0f;
   }
 }
 

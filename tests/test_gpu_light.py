@@ -23,7 +23,8 @@ def _samples(H, W, spp, rng):
     return d, code, pg.Samples.wrap(dev(d), dev(z), dev(z), dev(code), dev(z + 7))
 
 
-@pytest.mark.parametrize("W,H,spp", [(1, 1, 1), (2, 3, 2), (3, 1, 8), (5, 9, 3), (127, 8, 1), (129, 7, 2), (260, 17, 1)])
+@pytest.mark.parametrize("W,H,spp", [(1, 1, 1), (2, 3, 2), (3, 1, 8), (5, 9, 3), (127, 8, 1), (129, 7, 2), (260, 17, 1),
+                                     (1283, 307, 2), (1026, 767, 1)])  # the last two take four pixels a lane
 def test_light_field_rows_and_extremes(W, H, spp):
     rng = np.random.default_rng(100 * W + spp)
     scene = wl.make_scene(W, H, 5)
