@@ -129,8 +129,11 @@ def _ptr(t):
 
 
 def _stream():
+    """The current stream of the current device.  (As a raw handle: a
+    torch.cuda.Stream object costs several microseconds a call, which small
+    views wait for.)"""
     import torch
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def gamma_dtype_code(dtype) -> int:
