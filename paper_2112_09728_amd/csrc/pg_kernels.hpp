@@ -1176,16 +1176,21 @@ __device__ __forceinline__ void em_tile(const ParamsK &P, const ViewK &v, const 
   tile_write_back<Op, NT>(op, wb, me, me_in, g, t, in_image, plane, row_off(y0, v.pitch) + x0);
 }
 
-// Two-pass training tile (online EM from spp 4).  Above spp 1 the staged
-// records of every sample plane fill the LDS and few blocks share a CU (at
-// spp 4 and 32x8, 3 blocks: VALU 53% busy; at spp 8, 18% occupancy).  Here
-// the records of the first PG = ceil(spp/2) planes are staged, with one
+// Two-pass training tile (from spp 4).  Above spp 1 the staged records of
+// every sample plane fill the LDS and few blocks share a CU (at spp 8, two).
+// Here the records of the first PG = ceil(spp/2) planes are staged, with one
 // validity bit per candidate record of all planes; each pixel's list is built
 // once, as in em_tile, storing its entries of the first planes from the
 // front of its column and those of the last planes from the back; the E-step
 // runs over the first planes, the records area is restaged with the last
 // planes, and the same sums continue over them.  Each pass keeps the
 // training set's order, so the result does not depend on the tile shape.
+// What bounds it at 1080p and 8 spp (333 us; 381 before its records were
+// staged in groups and its lists kept by address): VALU issue 59% of the
+// cycles at 2.6 of 3 waves per SIMD; without any visit 205 us, with records
+// that hit the caches 293.  Reading the second pass's records ahead into
+// registers (355), windows on whole 128-byte lines (341) and two visits side by
+// side (345) gained nothing.
 
 // A group's records (REC) and validity bits (KEY) to the LDS of the two-pass
 // tile: records at their own item, bits at `bit_item` (the same unless the
@@ -1414,7 +1419,9 @@ struct NllCtx {
 // it: the picks of a pixel are examined once against the staged records and
 // only the kept ones visited, by lanes sorted to nearly equal lists.  (One
 // lane per pixel in image order visited all of its candidates: 24 visits a
-// wave at spp 4, where the sorted lists need about 11.)
+// wave at spp 4, where the sorted lists need about 15.)  4K, 4 spp: 709 us for
+// the loss and 781 for the gradient, VALU issue 83% of the cycles; 922 us each
+// before.
 template <bool LOSS, bool GRAD>
 struct NllOp {
   using Ctx = NllCtx;

@@ -179,10 +179,10 @@ constexpr Tile kTiles[] = {{32, 8}, {16, 16}, {64, 4}, {32, 4}, {16, 8}, {64, 2}
 // holds one block more per CU) and at 32x8 above (spp 7 317 against 328, spp 8
 // 336 against 343: 3 blocks per CU either way).
 // The single-pass tile (up to spp 3, and batch EM or the stale test above):
-// 32x8 up to spp 4; above, the staged records limit how many blocks share a
-// CU's LDS, and the shape that keeps the most waves resident wins: 16x16 at
-// spp 5 (266 us against 339 for 32x4), 16x8 at spp 6-8 (spp 8: 508 us
-// against 726).
+// 32x8 up to spp 4 (spp 1 113 us; 16x16 111, 64x8 110, but 5% behind at 4K and
+// 4% at 640x360; spp 3 167 against 170 at 16x16); above, the staged records
+// limit how many blocks share a CU's LDS, and the shape that keeps the most
+// waves resident wins: 16x16 at spp 5 (230 us), 16x8 at spp 6-8 (spp 8 440).
 Tile default_tile(int spp, bool two) {
   if (two) return spp <= 6 ? Tile{16, 16} : Tile{32, 8};
   return spp <= 4 ? Tile{32, 8} : (spp == 5 ? Tile{16, 16} : Tile{16, 8});
@@ -200,9 +200,11 @@ size_t tile_lds(Tile t, int spp, bool two) {
 // Whether a training launch takes the two-pass tile: online EM from spp 4
 // without the stale-history test (batch EM revisits the whole list every
 // iteration, and the test reads it before the E-step).  At 1080p EM per
-// frame: spp 8 382 us (16x16) against 503 single-pass, spp 4 230 against
-// 246; at spp 2 the single-pass tile already keeps 5 blocks per CU and the
-// second pass costs more than it gains (182 against 157 us).
+// frame, two passes against one at its best tile: spp 4 201 us against 214,
+// spp 6 252 against 312, spp 8 333 against 440 (spp 5 alone 237 against 230);
+// below, the single-pass tile already keeps 4 blocks or more per CU and the
+// second pass costs more than it gains (spp 3 190 against 168, spp 2 167
+// against 144).
 bool em_two_pass(int spp, int batch, uint32_t flags) { return spp >= 4 && !batch && !(flags & PG_STALE_RESET); }
 
 pg_status pick_tile(const pg_params *p, int spp, Tile &t, bool two = false) {
