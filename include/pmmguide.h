@@ -371,9 +371,9 @@ pg_status pg_batch_pack(const pg_batch_view *views, int32_t n_views, void *host_
  * re-packed tables of other frames and views as long as the dtype and the spp
  * groups with their tiles stay those of the capture and the views have no
  * more sampling tiles, and no group more training tiles, than at the capture
- * (a launch whose part of the table differs skips it: nothing of it is
- * written).  Views must not share
- * output buffers. */
+ * (a training launch whose group of the table has another tile, more spp, or
+ * spp on the other side of 4, where the training kernel changes, skips the
+ * group: nothing of it is trained).  Views must not share output buffers. */
 pg_status pg_frame_batched(const void *host_table, void *device_table, size_t bytes, void *stream);
 
 /* For callers that cannot allocate device memory (code under HIP graph

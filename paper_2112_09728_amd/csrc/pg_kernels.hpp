@@ -755,6 +755,7 @@ __device__ __forceinline__ void build_pick_table(int16_t *tab, int spp) {
 // planes [spp][TH+6][TW+8], the lists [spp+20][w h] uint16, the pick table
 // and, per pixel, the list's entries in the first pass [w h] uint8.  (Rows of
 // whole groups of four: two lanes' groups are one byte of bits.)
+__host__ __device__ constexpr bool em2_spp(int spp) { return spp >= 4; }  // (pmmguide.hip gives the figures)
 __host__ __device__ constexpr int em2_planes(int spp) { return (spp + 1) >> 1; }
 __host__ __device__ constexpr int em2_stride(int tw, int th) { return (tw + 8) * (th + 2 * kR); }
 __host__ __device__ constexpr size_t em2_bits_bytes(int tw, int th, int spp) {
@@ -1630,8 +1631,10 @@ __global__ __launch_bounds__(256) void k_rs_batched(const char *__restrict__ tab
 // tile in XCD bands (like k_em: with no state carried from tile to tile the
 // kernel fits 8 waves/SIMD; a persistent loop over tiles needed ~30 more
 // VGPRs).  `spp_cap` is the spp the dynamic LDS was sized for; a table whose
-// class differs from the launch (tile, spp, dtype, or more tiles than the
-// grid) is not processed.
+// class differs from the launch (tile, one or two passes, more spp, dtype, or
+// more tiles than the grid) is not processed.  (The tile alone does not tell
+// the passes apart: 32x8 is the default of both.  A two-pass launch cannot
+// train a class of few samples: its staging takes four records for granted.)
 template <typename TG, int TW, int TH, bool TWO>
 __global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(TH == 2 ? 1 : (TWO ? 5 : 8)))) void k_em_batched(const char *__restrict__ table, int dtype, int cls,
                                                        int spp_cap) {
@@ -1640,7 +1643,7 @@ __global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(TH == 2 
   const BatchHeader *hd = reinterpret_cast<const BatchHeader *>(table);
   if (hd->dtype != dtype || cls >= hd->n_classes) return;
   const BatchClass c = hd->cls[cls];
-  if (c.spp > spp_cap || c.tile_w != TW || c.tile_h != TH) return;
+  if (c.spp > spp_cap || em2_spp(c.spp) != TWO || c.tile_w != TW || c.tile_h != TH) return;
   const int n_views = hd->n_views;
   const BatchViewK *vs = batch_views(table);
   const int n = c.em_end - c.em_begin;

@@ -205,7 +205,7 @@ size_t tile_lds(Tile t, int spp, bool two) {
 // below, the single-pass tile already keeps 4 blocks or more per CU and the
 // second pass costs more than it gains (spp 3 190 against 168, spp 2 167
 // against 144).
-bool em_two_pass(int spp, int batch, uint32_t flags) { return spp >= 4 && !batch && !(flags & PG_STALE_RESET); }
+bool em_two_pass(int spp, int batch, uint32_t flags) { return em2_spp(spp) && !batch && !(flags & PG_STALE_RESET); }
 
 pg_status pick_tile(const pg_params *p, int spp, Tile &t, bool two = false) {
   if (p->tile_w == 0 && p->tile_h == 0) {

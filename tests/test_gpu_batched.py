@@ -185,3 +185,48 @@ def test_batched_view_against_oracle():
     e = assert_gamma_close(host(bg.state(i)), g2, TOL_EM_FRAME, mask=~underflow_mask(stats),
                            what="batched view, frame 2")
     say(f"  EM {e}")
+
+
+@pytest.mark.parametrize("spp", [1, 2, 3])
+def test_replay_skips_a_group_trained_by_the_other_kernel(spp):
+    """A graph captured with an 8 spp view (two-pass training, 32x8 tiles)
+    replays a table whose view has so few spp that it would train in one pass
+    with tiles of the same shape: the training launch leaves the view as
+    sampling alone does; a table of 8 spp again is trained."""
+    W, H, seed = 70, 37, wl.SEED_BASE + 90
+    fr = wl.Sequence(W, H, seed).frame(0)
+    cur = pg.DeviceFrame(fr)
+    lights = pg.lights_struct(fr["lights"], float(fr["ambient"]))
+
+    def view_of(n):
+        s, g = pg.Samples(n, H, W), pg.new_gamma(H, W)
+        b = pg.PgBatchView()
+        b.params, b.cur, b.gamma_out = pg.params(seed, frame=0), cur.view.c, pg._gamma(g)
+        b.samples, b.vis, b.lights = s.c, cur.vis.data_ptr(), lights
+        return b, s, g
+
+    table = torch.empty(pg.batch_table_bytes(1), dtype=torch.uint8, pin_memory=True)
+    device_table = torch.empty_like(table, device="cuda")
+    captured, few = view_of(8), view_of(spp)
+    pg.batch_pack([captured[0]], table)
+    pg.frame_batched(table, device_table)
+    torch.cuda.synchronize()
+    trained = captured[2].clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, capture_error_mode="thread_local"):
+        pg.frame_batched(table, device_table)
+    say(f"case: captured at 8 spp, replayed at {spp}")
+    want, s_want = pg.new_gamma(H, W), pg.Samples(spp, H, W)
+    pg.reproject_sample(pg.params(seed, frame=0), cur.view, None, None, want, s_want)
+    for i in range(3):
+        few[2].fill_(-1.0)
+        pg.batch_pack([few[0]], table)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(few[2], want) and torch.equal(few[1].dir, s_want.dir), i
+        captured[2].fill_(-1.0)
+        pg.batch_pack([captured[0]], table)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(captured[2], trained), i
+    assert not torch.equal(trained, want)
