@@ -1461,16 +1461,28 @@ struct NllOp {
     const float w = r.w * f * l.z;
     const float z1 = rx * c.T.i11;
     const float z2 = fmaf(ry, c.T.i22, z1 * c.T.c21);
-    float ga = c.T.pi_norm * __builtin_amdgcn_exp2f(-0.72134752044448170368f * fmaf(z1, z1, z2 * z2));
+    const float e = -0.72134752044448170368f * fmaf(z1, z1, z2 * z2);
+    float ga = c.T.pi_norm * __builtin_amdgcn_exp2f(e);
     float D = fmaf(c.one_m_pi, pb, ga), off = 0.0f;
-    if (D < 0x1p-100f) {  // the hardware logarithm and reciprocal take subnormals for zero
-      ga *= 0x1p64f;
-      D *= 0x1p64f;
-      off = 64.0f;
+    // The hardware exponential gives 0 below 2^-126, and the logarithm and the
+    // reciprocal take subnormals for 0: where so little is left (1 - pi is 0 or
+    // at least 2^-24, so that p_b no longer counts), the Gaussian is taken 2^32
+    // times larger before it is rounded, which reaches below the smallest
+    // subnormal.  (e + 32 is exact for e < -32.)  One uniform branch for the
+    // wave, seldom taken.
+    const bool far = D < 0x1p-64f;
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(far) != 0, 0)) {
+      const float gs = e < -32.0f ? c.T.pi_norm * __builtin_amdgcn_exp2f(e + 32.0f) : ga * 0x1p32f;
+      ga = far ? gs : ga;
+      D = far ? fmaf(c.one_m_pi * 0x1p32f, pb, gs) : D;
+      off = far ? 32.0f : 0.0f;
     }
     if (LOSS) a.loss = fmaf(w, off - __builtin_amdgcn_logf(D), a.loss);
     if (GRAD) {
-      const float gam = D > 0.0f ? ga * __builtin_amdgcn_rcpf(D) : 0.0f;
+      // the quotient corrected by its remainder, as a division rounds it (1
+      // where the Gaussian is alone)
+      const float Dn = fmaxf(D, 1.17549435e-38f), rD = __builtin_amdgcn_rcpf(Dn), q = ga * rD;
+      const float gam = fmaf(fmaf(-q, Dn, ga), rD, q);
       // Sigma^-1 r = L^-T z
       const float vx = c.T.i11 * fmaf(c.T.c21, z2, z1), vy = c.T.i22 * z2;
       const float wg = w * gam, hg = -0.5f * wg;

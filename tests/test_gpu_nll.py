@@ -172,3 +172,44 @@ def test_nll_of_trained_records_at_tile_edges(W, H, spp):
             e = np.abs(g[c] - grad_o[c]) / (np.abs(grad_o[c]) + 1e-3 * (np.abs(grad_o[c]).max() + 1e-30))
             assert np.quantile(e, 0.99) <= 1e-4 and e.max() <= 1e-3, c
         assert (g[6:] == 0).all() and (n[idle] == 0).all() and (g[:, idle] == 0).all()
+
+
+@pytest.mark.parametrize("spp", [1, 4])
+def test_nll_where_only_a_far_gaussian_is_left(spp):
+    """A weight pi that rounds to 1 (logit 100) leaves the Gaussian alone, and
+    every sample 10 to 14.3 standard deviations from it: densities down to
+    exp(-102), below FP32's normal numbers.  The loss and its gradient stay
+    those of the Gaussian (posterior 1).  Bounds: u carries up to 4 ulp (2.4e-7)
+    and the deviation z = |u - mu| / 0.034 up to 14.3, so z^2 / 2 (50 and more)
+    is off by 1e-4 at most, 2e-6 of the loss; the weight's BRDF adds 1e-5."""
+    say(f"case: nll of far samples, spp {spp}")
+    W, H = 45, 19
+    one = np.ones((H, W), np.float32)
+    scene = dict(normal=np.stack([0 * one, 0 * one, one]), view_dir=np.stack([0 * one, 0.6 * one, 0.8 * one]),
+                 depth=one, roughness=0.5 * one, albedo=0.5 * one)
+    t, b = O.onb(np.array([[0.0, 0.0, 1.0]]))
+    u = np.array([[0.12, 0.15]])
+    l = O.sq2hemi(u)[0]
+    w = l[0] * t[0] + l[1] * b[0] + l[2] * np.array([0.0, 0.0, 1.0])
+    rec = dict(dir=np.broadcast_to(w.astype(np.float32)[:, None, None, None], (3, spp, H, W)).copy(),
+               pdf_mix=np.full((spp, H, W), 0.3, np.float32), pdf_brdf=np.full((spp, H, W), 0.3, np.float32),
+               strategy=np.ones((spp, H, W), np.uint8), radiance=np.full((spp, H, W), 2.0, np.float32))
+    z = np.linspace(10.0, 14.3, W * H).reshape(H, W)
+    sd, ang = np.sqrt(0.03 ** 2 + 2.5e-4), np.linspace(0.1, 1.4, W)[None, :]
+    th = np.stack([u[0, 0] + z * sd * np.cos(ang), u[0, 1] + z * sd * np.sin(ang), 0.03 * one, 0 * one, 0.03 * one,
+                   100 * one, 0 * one, 16 * one]).astype(np.float32)
+    p = pg.params(7, frame=2)
+    s = pg.Samples.wrap(*(dev(rec[k]) for k in ("dir", "pdf_mix", "pdf_brdf", "strategy", "radiance")))
+    view = gpu_view(scene)
+    nll, grad = pg.nll_backward(p, view, s, dev(th))
+    loss_only, _ = pg.nll_backward(p, view, s, dev(th), want_grad=False)
+    _, grad_only = pg.nll_backward(p, view, s, dev(th), want_nll=False)
+    torch.cuda.synchronize()
+    nll_o, grad_o = O.nll(O.params(7, frame=2), O.OView(scene), rec, th)
+    assert np.isfinite(nll_o).all() and nll_o.min() > 0
+    for n, g in ((host(nll), host(grad)), (host(loss_only), host(grad_only))):
+        assert np.isfinite(n).all() and np.isfinite(g).all()
+        assert (np.abs(n - nll_o) <= 2e-5 * nll_o).all()
+        for c in range(5):
+            assert (np.abs(g[c] - grad_o[c]) <= 2e-5 * (np.abs(grad_o[c]) + 1e-3 * np.abs(grad_o[c]).max())).all(), c
+        assert (g[5] == 0).all()
