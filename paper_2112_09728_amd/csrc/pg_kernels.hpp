@@ -226,15 +226,15 @@ struct LightsK {
   float l[8][5];
 };
 
-// exp(x) to about 1.5 ulp: the hardware exp2 of the rounded product x log2(e),
-// corrected by the product's rounding error (first order).  Below 2^-126 it
-// gives 0.  (The clamps act only where the product or the result is infinite,
-// and keep inf - inf and 0 * inf out of the correction.)
+// exp(x) = 2^n exp2(x log2(e) - n) to about 1 ulp over FP32's whole range,
+// subnormal results included: n whole, the rest formed in two fused steps (the
+// second adds what log2(e) lost to FP32) and at most 1/2, where the hardware
+// exp2 is accurate.  Beyond the range the rest keeps the sign and the clamp of
+// n keeps inf - inf from x = +-inf: 0 and inf there, NaN for NaN.
 __device__ __forceinline__ float exp_fast(float x) {
-  const float t = x * 1.44269504088896340736f;
-  const float lo = fmaf(x, 1.92596299e-8f, fmaf(x, 1.44269504088896340736f, -t));
-  const float e = __builtin_amdgcn_exp2f(t);
-  return fmaf(fminf(e, 3.40282347e38f) * 0.693147180559945309417f, __builtin_amdgcn_fmed3f(lo, -1.0f, 1.0f), e);
+  const float n = rintf(__builtin_amdgcn_fmed3f(x * 1.44269504088896340736f, -160.0f, 160.0f));
+  const float y = fmaf(x, 1.92596299e-8f, fmaf(x, 1.44269504088896340736f, -n));
+  return ldexpf(__builtin_amdgcn_exp2f(y), (int)n);
 }
 
 __device__ __forceinline__ float light_radiance(const LightsK &Lt, uint32_t bits, V3 wdir) {

@@ -63,3 +63,33 @@ def test_ceiling_table_and_memory_lattice_agree(W, H, spp):
         torch.cuda.synchronize()
         out.append((host(s.radiance).copy(), host(hit)))
     assert (out[0][0] == out[1][0]).all() and (out[0][1] == out[1][1]).all()
+
+
+def test_light_field_over_the_whole_range_of_the_exponential():
+    """Terms below FP32's normal numbers count (a sharp light of intensity 1e38),
+    and so do those next to its largest number (the direction opposite to a light
+    that grows away from its axis).  Bounds: the argument carries sqrt(2 |x|
+    lambda) 2^-23 (1.2e-5 at x = -100, lambda = 50) and the exponential a few ulp,
+    below 2^-126 two steps of 2^-149."""
+    W, H, spp = 257, 33, 2
+    rng = np.random.default_rng(77)
+    scene = wl.make_scene(W, H, 8)
+    d, code, s = _samples(H, W, spp, rng)
+    axis = np.array([0.6, 0.0, 0.8], np.float32)
+    vis = np.full((H, W), 1, np.uint8)
+    lights = np.array([[*axis, 50, 1e38]], np.float32)
+    pg.light_field(pg.lights_struct(lights, 0.0), gpu_view(scene), dev(vis), s)
+    torch.cuda.synchronize()
+    got, want = host(s.radiance).astype(np.float64), O.light(lights, 0.0, vis, d, code)
+    assert ((want > 0) & (want < 1e38 * 2.0 ** -126)).sum() > 500  # (the subnormal terms)
+    assert (np.abs(got - want) <= 3e-5 * want + 1e38 * 2.0 ** -148).all()
+    # x = 88.72283, the largest argument with a finite exponential
+    x = np.float32(88.72283)
+    d[:] = np.array([0, 0, -1], np.float32)[:, None, None, None]
+    s.dir.copy_(dev(d))
+    lights = np.array([[0, 0, 1, -x / 2, 1e-30]], np.float32)
+    pg.light_field(pg.lights_struct(lights, 0.0), gpu_view(scene), dev(vis), s)
+    torch.cuda.synchronize()
+    got, live = host(s.radiance).astype(np.float64), (code == 1) | (code == 2)
+    want = float(np.float32(1e-30)) * np.exp(float(x))
+    assert (np.abs(got[live] - want) <= 1e-6 * want).all()
