@@ -598,13 +598,14 @@ __device__ __forceinline__ float ceiling_emission(const CeilingK &C, float yx, f
 }
 
 // The lamp table of a block: the lattice with a border of two dark cells, so
-// that no neighbour needs a test, and 1 / (2 r^2) in the place of r.
+// that no neighbour needs a test, and 1 / (2 r^2) in the place of r (not 0 in
+// the dark cells: their distance may be infinite).
 __host__ __device__ constexpr int ceiling_cells(int nx, int ny) { return (nx + 4) * (ny + 4); }
 __device__ __forceinline__ void load_lamps(const CeilingK &C, float4 *tab) {
   const int w = C.nx + 4, n = ceiling_cells(C.nx, C.ny);
   for (int k = threadIdx.x; k < n; k += 256) {
     const int j = k / w - 2, i = k - (j + 2) * w - 2;
-    float4 l = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    float4 l = make_float4(0.0f, 0.0f, 1.0f, 0.0f);
     if (i >= 0 && j >= 0 && i < C.nx && j < C.ny) {
       l = reinterpret_cast<const float4 *>(C.lamps)[j * C.nx + i];
       l.z = 1.0f / (2.0f * l.z * l.z);

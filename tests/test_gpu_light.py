@@ -93,3 +93,34 @@ def test_light_field_over_the_whole_range_of_the_exponential():
     got, live = host(s.radiance).astype(np.float64), (code == 1) | (code == 2)
     want = float(np.float32(1e-30)) * np.exp(float(x))
     assert (np.abs(got[live] - want) <= 1e-6 * want).all()
+
+
+def test_ceiling_border_far_from_the_origin():
+    """A lattice so far out that the square of a position overflows: the dark
+    cells around the lamps of the table add nothing (no 0 times infinity), and
+    the radiance is that of the lattice read from memory."""
+    W, H, spp = 61, 9, 2
+    rng = np.random.default_rng(5)
+    scene = wl.make_scene(W, H, 6)
+    d, _, s = _samples(H, W, spp, rng)
+    per, x0, n = 1e19, 1e20, 3
+    lamps = np.zeros((n, n, 4), np.float32)
+    lamps[..., 0] = x0 + per * (np.arange(n)[None, :] + 0.5)
+    lamps[..., 1] = x0 + per * (np.arange(n)[:, None] + 0.5)
+    lamps[..., 2], lamps[..., 3] = 4e18, 3.0
+    big = np.zeros((60, 60, 4), np.float32)  # no room in LDS
+    big[..., 2] = 1.0
+    big[:n, :n] = lamps
+    pos = np.stack([rng.uniform(x0 - per, x0 + 4 * per, (H, W)), rng.uniform(x0 - per, x0 + 4 * per, (H, W)),
+                    rng.uniform(0, 5, (H, W))]).astype(np.float32)
+    out = []
+    for t in (lamps, big):
+        c = pg.Ceiling(dict(z=32.0, period=per, x0=x0, y0=x0, ambient=0.05, lamps=t))
+        hit = torch.empty((spp, H, W), device="cuda")
+        pg.light_ceiling(c, gpu_view(scene), dev(pos), s, hit)
+        torch.cuda.synchronize()
+        out.append(host(s.radiance).copy())
+    # (cells beyond the 3x3 lamps are dark in both lattices)
+    inside = (pos[0] < x0 + 3.9 * per) & (pos[1] < x0 + 3.9 * per)
+    assert np.isfinite(out[0]).all() and (out[0][:, inside] > 0.06).any()
+    assert (out[0][:, inside] == out[1][:, inside]).all()
