@@ -335,9 +335,10 @@ __device__ __forceinline__ void lobes_visit(const LobesCtx<K> &c, float4 r, floa
 // image are large; differences of nearby ones are small and exact), and one
 // without an interaction holds its direction with the weight negated.
 __device__ __forceinline__ float4 vpl_record(V3 dir, float w, float t, V3 xq, V3 cref) {
-  if (!isfinite(t)) return make_float4(dir.x, dir.y, dir.z, -w);
   const V3 d = normalized(dir);
-  return make_float4(fmaf(t, d.x, xq.x - cref.x), fmaf(t, d.y, xq.y - cref.y), fmaf(t, d.z, xq.z - cref.z), w);
+  const bool hit = isfinite(t);
+  return make_float4(hit ? fmaf(t, d.x, xq.x - cref.x) : dir.x, hit ? fmaf(t, d.y, xq.y - cref.y) : dir.y,
+                     hit ? fmaf(t, d.z, xq.z - cref.z) : dir.z, hit ? w : -w);
 }
 
 template <int TW, int TH>
@@ -385,12 +386,10 @@ __device__ __forceinline__ void stage_records_vpl(const ViewK &v, const SamplesK
     const int e = s * SA + (int)__umul24((uint32_t)sy, (uint32_t)SW) + 4 * g - 1;
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      if ((j > 0 || g > 0) && (j < 3 || g < G - 1)) {
-        float4 r = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (group_valid(q, j))
-          r = vpl_record(V3{q.x[j], q.y[j], q.z[j]}, group_weight(q, j), t[j], V3{x[j], y[j], z[j]}, cref);
-        lds[e + j] = r;
-      }
+      // (no branch on what trains: a record of weight 0 is never read)
+      if ((j > 0 || g > 0) && (j < 3 || g < G - 1))
+        lds[e + j] = vpl_record(V3{q.x[j], q.y[j], q.z[j]}, group_valid(q, j) ? group_weight(q, j) : 0.0f, t[j],
+                                V3{x[j], y[j], z[j]}, cref);
   }
 }
 
@@ -482,7 +481,12 @@ __device__ __forceinline__ void lobes_update(const ParamsK &P, const ViewK &v, i
 // pixel are re-derived from the staged y).
 // Two lobes (directional) fit 72 VGPRs without spilling, 7 waves per SIMD
 // instead of the 6 that the compiler's own choice (75) leaves: EM -4%; at
-// 8 waves, or with VPL at 7, it spills.
+// 8 waves, or with VPL at 7, it spills.  One lobe fits 8 waves (54 VGPRs, 61
+// with VPL) and is told so: positional training at 1080p, 1 spp, 103 us against
+// 108 without the hint, the same above.  With VPL that holds only as long as
+// the staging leaves room: the tile's reference point in vector registers and
+// a branch per record made it spill (1080p, 2 spp: 144 us, now 140; 8 spp 764,
+// now 734).
 template <int K, int TW, int TH, bool VPL = false>
 __global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(K == 1 ? 8 : (K == 2 && !VPL ? 7 : 1)))) void k_lobes_em(ParamsK P, ViewK v, SamplesK S, float *__restrict__ gamma,
                                                      int tiles_x, int n_tiles, const float *__restrict__ pos,
@@ -512,8 +516,9 @@ __global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(K == 1 ?
   }
   V3 cref = V3{0.0f, 0.0f, 0.0f};
   if (VPL) {
-    const int ci = min(ty0, v.H - 1) * v.pitch + min(tx0, v.W - 1);
-    cref = load3(pos, plane, ci);
+    // (uniform: scalar loads, no vector registers)
+    const float *c = pos + (min(ty0, v.H - 1) * v.pitch + min(tx0, v.W - 1));
+    cref = V3{c[0], c[plane], c[2 * plane]};
     stage_records_vpl<TW, TH>(v, S, pos, hit, cref, lds, tx0, ty0);
   } else {
     if (few_records(v, S))

@@ -347,3 +347,12 @@ def test_batch_pack_tile_per_spp_group():
     bad = [_bview(spp=1, base=0, tile_w=16, tile_h=16), _bview(spp=1, base=1 << 16, tile_w=32, tile_h=8)]
     st, msg, _ = _pack(bad)
     assert st == pg.PG_ERR_ARG and "different training tiles" in msg and "view 1" in msg, msg
+
+
+def test_no_kernel_uses_scratch_memory():
+    """No kernel of the built library spills registers (the code object's notes
+    hold every kernel's scratch bytes a lane)."""
+    data = open(pg.LIB_PATH, "rb").read()
+    key = b".private_segment_fixed_size"
+    sizes = [data[m.end()] for m in re.finditer(re.escape(key), data)]  # msgpack: 0x00 is the integer 0
+    assert len(sizes) > 100 and set(sizes) == {0}
