@@ -174,10 +174,11 @@ __device__ __forceinline__ int reproject_pixel(const ParamsK &P, const ViewK &cu
 // First-bounce estimate of one pixel: the mean over its samples of
 // f_r L cos / D (null samples count zero), the Monte Carlo estimator of the
 // reflected radiance with the mixture density of the samples.  Bound by HBM
-// (21 B a record, 36 B a pixel); the records of four samples are loaded before
-// the first is used, whatever their strategy: one sample at a time, its code
-// tested before its other loads, took 92.3 us at 1080p and 8 spp (now 79.6,
-// 5.3 TB/s).
+// (21 B a record, 36 B a pixel).  All of a record is loaded before any of it is
+// tested: with the strategy tested first, its other loads waited for that one
+// (1080p: 90.8 us at 8 spp, now 77.7: 5.4 TB/s; 19.7 and 19.1 at 1 spp).  The
+// records of four samples in flight cost 19 registers and, where there are not
+// as many samples, loads (1 spp 20.7, 3 spp 32.7 against 30.0, 8 spp 80.8).
 __global__ __launch_bounds__(256) void k_estimate(ParamsK P, ViewK v, SamplesK S, float *__restrict__ out) {
   int x, y;
   stream_xy(v.W, v.H, x, y);
@@ -190,28 +191,20 @@ __global__ __launch_bounds__(256) void k_estimate(ParamsK P, ViewK v, SamplesK S
   float acc = 0.0f;
   if (dot3(n, o) > 0.0f) {
     const Pixel px = make_pixel(P, n, o, rough, albedo);
-    for (int s0 = 0; s0 < S.spp; s0 += 4) {
-      uint32_t code[4];
-      float D[4], L[4];
-      V3 w[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        // (past the last sample: the last one again, masked below)
-        const int r = min(s0 + j, S.spp - 1) * plane + idx;
-        code[j] = at(S.strat, r);
-        D[j] = at(S.pmix, r);
-        L[j] = at(S.L, r);
-        w[j] = load3(S.dir, splane, r);
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (s0 + j >= S.spp || !(code[j] == 1 || code[j] == 2) || !(D[j] > 0.0f)) continue;
-        const V3 l = to_local(px.f, normalized(w[j]));
-        if (l.z <= 0.0f) continue;
-        float f, pb;
-        brdf_eval(px, l, f, pb);
-        acc += f * L[j] * l.z / D[j];
-      }
+    for (int s = 0; s < S.spp; ++s) {
+      const int r = s * plane + idx;
+      const uint32_t code = at(S.strat, r);
+      const float D = at(S.pmix, r);
+      float L = at(S.L, r);
+      V3 w = load3(S.dir, splane, r);
+      // (keeps the compiler from moving these loads behind the test)
+      asm volatile("" : "+v"(L), "+v"(w.x), "+v"(w.y), "+v"(w.z));
+      if (!(code == 1 || code == 2) || !(D > 0.0f)) continue;
+      const V3 l = to_local(px.f, normalized(w));
+      if (l.z <= 0.0f) continue;
+      float f, pb;
+      brdf_eval(px, l, f, pb);
+      acc += f * L * l.z / D;
     }
     acc /= (float)S.spp;
   }
