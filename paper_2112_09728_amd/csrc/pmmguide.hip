@@ -157,6 +157,21 @@ dim3 stream_grid(int W, int H) { return dim3(((W + 63) / 64) * ((H + 3) / 4)); }
 // 5.7 against 6.1, 1080p 8.1 against 10.4).
 constexpr int64_t kLightFourRecords = 3 << 18;
 
+// Whether the ceiling's blocks hold the lamp table (`cells` with its border, 16
+// bytes each) in LDS; n tiles of 64x4 pixels.  A block fills its table once, at
+// a cost that grows with the cells, and then reads nine lamps a sample from LDS
+// instead of memory (1080p, 1640 cells: 18.8 against 23.2 us at 1 spp, 52
+// against 73 at 4).  With one sample a lane and up to one tile a block that does
+// not pay for more than 1024 cells (640x360 at 1 spp: 1024 cells 5.0 against 4.8
+// us, 1640 cells 5.8 and 4.9; 64x64: 3.7 and 2.9, 4.4 and 2.9), and above 1920
+// cells only 4 blocks fit a CU, which up to 2 spp costs more than the table
+// gains (1080p, 2025 cells: 28.2 against 23.2 us at 1 spp, 44 and 40 at 2, 74
+// and 76 at 4).
+bool ceiling_table(int64_t cells, int n, int spp) {
+  if (spp >= 3) return cells <= 2048;
+  return cells <= (spp == 2 || n >= 1536 ? 1920 : 1024);
+}
+
 template <typename F>
 pg_status dispatch_dtype(int dtype, F &&f) {
   switch (dtype) {
@@ -752,11 +767,9 @@ pg_status pg_light_ceiling(const pg_ceiling *c, const pg_view *v, const float *p
   C.lamps = c->lamps;
   const ViewK V = to_k(v);
   const SamplesK S = to_k(samples);
-  // the lamp table in LDS up to 32 KiB (5 blocks a CU), read by as many blocks
-  // as that keeps resident on 256 CUs
   const int n = (int)stream_grid(V.W, V.H).x;
   const int64_t cells = ((int64_t)C.nx + 4) * ((int64_t)C.ny + 4);
-  if (cells * 16 <= 32 * 1024)
+  if (ceiling_table(cells, n, S.spp))  // 1280 blocks: 5 a CU, as many as 30 KiB each leaves resident
     hipLaunchKernelGGL((k_light_ceiling<true>), dim3(n < 1280 ? n : 1280), dim3(256), (size_t)cells * 16,
                        (hipStream_t)stream, C, V, position, S, hit_dist, n);
   else

@@ -124,3 +124,45 @@ def test_ceiling_border_far_from_the_origin():
     inside = (pos[0] < x0 + 3.9 * per) & (pos[1] < x0 + 3.9 * per)
     assert np.isfinite(out[0]).all() and (out[0][:, inside] > 0.06).any()
     assert (out[0][:, inside] == out[1][:, inside]).all()
+
+
+@pytest.mark.parametrize("nx,ny,spp", [(1, 500, 1), (500, 1, 2), (47, 44, 3), (40, 30, 1), (28, 28, 1), (39, 40, 2),
+                                       (42, 40, 2)])
+def test_ceiling_lattices_against_the_oracle(nx, ny, spp):
+    """Lattices on either side of the rule that puts the lamps into LDS (2520 to
+    2448 cells: never; 1496 at 1 spp and 2024 at 2: not in a view this small; 1024
+    and 1892: yes), one lamp wide and high, with rays that hit the border cells
+    and beyond.  A position up to 1000 from the origin is known to 6e-5 and the
+    emission's relative slope is at most d / r^2 = 8 / 4: 1e-3 leaves room."""
+    W, H, per = 261, 19, 4.0
+    rng = np.random.default_rng(nx + 7 * ny)
+    scene = wl.make_scene(W, H, 6)
+    d, code, s = _samples(H, W, spp, rng)
+    x0, y0 = -0.5 * per * nx, -0.5 * per * ny
+    lamps = np.stack([x0 + per * (np.arange(nx)[None, :] + rng.uniform(0.2, 0.8, (ny, nx))),
+                      y0 + per * (np.arange(ny)[:, None] + rng.uniform(0.2, 0.8, (ny, nx))),
+                      rng.uniform(2, 3, (ny, nx)), rng.uniform(2, 30, (ny, nx))], -1).astype(np.float32)
+    c = dict(z=2.0, period=per, x0=x0, y0=y0, ambient=0.05, lamps=lamps)
+    pos = np.stack([rng.uniform(x0 - 2 * per, -x0 + 2 * per, (H, W)), rng.uniform(y0 - 2 * per, -y0 + 2 * per, (H, W)),
+                    rng.uniform(0, 1, (H, W))]).astype(np.float32)
+    # rays that rise within 45 degrees of the vertical, and some that fall
+    d[2] = np.where(rng.random(d[2].shape) < 0.9, np.abs(d[2]) + 0.7, -np.abs(d[2]) - 0.1)
+    d = (d / np.linalg.norm(d, axis=0)).astype(np.float32)
+    s.dir.copy_(dev(d))
+    hit = torch.empty((spp, H, W), device="cuda")
+    pg.light_ceiling(pg.Ceiling(c), gpu_view(scene), dev(pos), s, hit)
+    torch.cuda.synchronize()
+    L_o, t_o = O.light_ceiling(c, O.OView(scene), pos, d, code)
+    L, t = host(s.radiance), host(hit)
+    live = (code == 1) | (code == 2)
+    up = live & np.isfinite(t_o)
+    assert up.sum() > 100 and (np.isinf(t) == np.isinf(t_o)).all()
+    assert (np.abs(t[up] - t_o[up]) <= 1e-5 * t_o[up]).all()
+    # a cell is chosen by a floor, which may differ for a point on its edge
+    y = pos[:2, None] + t_o[None] * d[:2]
+    with np.errstate(invalid="ignore"):
+        f = np.abs((y - np.array([x0, y0]).reshape(2, 1, 1, 1)) / per)
+        edge = (np.abs(f - np.round(f)) < 1e-4).any(0)
+    ok = live & ~(edge & up)
+    assert (np.abs(L[ok] - L_o[ok]) <= 1e-3 * L_o[ok]).all()
+    assert (L[~live] == 0).all()
