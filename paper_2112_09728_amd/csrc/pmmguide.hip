@@ -186,6 +186,7 @@ pg_status dispatch_dtype(int dtype, F &&f) {
 struct Tile {
   int w, h;
 };
+constexpr size_t kMaxTileLds = 64 * 1024;
 constexpr Tile kTiles[] = {{32, 8}, {16, 16}, {64, 4}, {32, 4}, {16, 8}, {64, 2}, {32, 16}, {64, 8}};
 
 // Default training tile per spp (1080p pan, EM per frame).  The two-pass
@@ -232,7 +233,7 @@ pg_status pick_tile(const pg_params *p, int spp, Tile &t, bool two = false) {
     if (!found) return fail(PG_ERR_UNSUPPORTED, "tile %dx%d is not built", p->tile_w, p->tile_h);
     t = Tile{p->tile_w, p->tile_h};
   }
-  if (tile_lds(t, spp, two) > 64 * 1024)
+  if (tile_lds(t, spp, two) > kMaxTileLds)
     return fail(PG_ERR_UNSUPPORTED, "tile %dx%d with spp %d needs %zu B of LDS (> 64 KiB)", t.w, t.h, spp,
                 tile_lds(t, spp, two));
   return PG_OK;
@@ -276,10 +277,14 @@ void launch_nll_t(const ParamsK &P, const ViewK &v, const SamplesK &S, const Nll
   const int n = tx * ty;
   const bool two = em_two_pass(S.spp, 0, 0);
   const size_t lds = tile_lds(Tile{TW, TH}, S.spp, two);
-  if (two)
-    hipLaunchKernelGGL((k_nll<TW, TH, LOSS, GRAD, true>), dim3(n), dim3(TW * TH), lds, st, P, v, S, op, tx, n);
-  else
-    hipLaunchKernelGGL((k_nll<TW, TH, LOSS, GRAD, false>), dim3(n), dim3(TW * TH), lds, st, P, v, S, op, tx, n);
+  // (no two-pass kernel of the tiles that pg_nll_backward refuses from 4 spp)
+  if constexpr (em_lds_front(TW, TH, 4) <= kMaxTileLds) {
+    if (two) {
+      hipLaunchKernelGGL((k_nll<TW, TH, LOSS, GRAD, true>), dim3(n), dim3(TW * TH), lds, st, P, v, S, op, tx, n);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_nll<TW, TH, LOSS, GRAD, false>), dim3(n), dim3(TW * TH), lds, st, P, v, S, op, tx, n);
 }
 
 template <bool LOSS, bool GRAD>

@@ -213,3 +213,40 @@ def test_nll_where_only_a_far_gaussian_is_left(spp):
         for c in range(5):
             assert (np.abs(g[c] - grad_o[c]) <= 2e-5 * (np.abs(grad_o[c]) + 1e-3 * np.abs(grad_o[c]).max())).all(), c
         assert (g[5] == 0).all()
+
+
+@pytest.mark.parametrize("spp", [1, 3, 4, 8])
+def test_nll_tile_shapes_bitwise_identical(spp):
+    """Every tile that pg_nll_backward takes gives the same bits, the loss and the
+    gradient together and each on its own (the default is 32x8 up to 3 spp and at
+    7 and 8, 16x16 between); the others are refused: the records of all planes,
+    the lists and the pick table must fit 64 KiB, although two passes from 4 spp
+    would need less."""
+    say(f"case: nll tile invariance, spp {spp}")
+    W, H, seed = 99, 61, 6100 + spp
+    scene = wl.make_scene(W, H, seed)
+    rng = np.random.default_rng(seed)
+    view = gpu_view(scene)
+    p0 = pg.params(seed, frame=3)
+    s = pg.Samples(spp, H, W)
+    pg.sample_mis(p0, view, dev(random_gamma(H, W, rng, k_lo=0)), s)
+    pg.light_field(pg.lights_struct(scene["lights"], float(scene["ambient"])), view, dev(scene["vis"]), s)
+    th = _theta(H, W, rng)
+    th[7] = rng.integers(0, 17, (H, W))
+    th, go = dev(th), dev(rng.uniform(0.5, 2.0, (H, W)).astype(np.float32))
+    nll0, grad0 = pg.nll_backward(p0, view, s, th, grad_out=go)
+    assert torch.isfinite(nll0).all() and (grad0[:6].abs().amax((1, 2)) > 0).all()
+    for tw, th_ in pg.guide.TILES:
+        say(f"  tile {tw}x{th_}")
+        p = pg.params(seed, frame=3, tile_w=tw, tile_h=th_)
+        lds = (tw + 6) * (th_ + 6) * spp * 16 + (spp + 20) * tw * th_ * 2 + ((96 * spp + 15) & ~15)
+        if lds > 64 * 1024:
+            with pytest.raises(RuntimeError, match="LDS"):
+                pg.nll_backward(p, view, s, th, grad_out=go)
+            continue
+        nll, grad = pg.nll_backward(p, view, s, th, grad_out=go)
+        loss_only, _ = pg.nll_backward(p, view, s, th, want_grad=False)
+        _, grad_only = pg.nll_backward(p, view, s, th, grad_out=go, want_nll=False)
+        torch.cuda.synchronize()
+        assert torch.equal(nll, nll0) and torch.equal(loss_only, nll0), (tw, th_)
+        assert torch.equal(grad, grad0) and torch.equal(grad_only, grad0), (tw, th_)
