@@ -127,3 +127,77 @@ def test_pitch_larger_than_width(W, H, spp):
     assert np.array_equal(_valid(est, W).view(np.int32), host(est_ref).view(np.int32))
     assert _pad_untouched(est, W)
     say("  5 frames + pdf + estimate bit-identical, padding untouched")
+
+
+@pytest.mark.parametrize("W,H,spp", [(61, 33, 4), (45, 29, 5), (70, 19, 8), (1027, 771, 1)])
+def test_pitch_two_pass_training_and_wide_light_field(W, H, spp):
+    """The same for the two-pass training tile (from 4 spp, the second at 5 with
+    planes of unequal halves, 32x8 tiles at 8) and for the light field's four
+    pixels a lane (from 786432 records; rows of 1027)."""
+    test_pitch_larger_than_width(W, H, spp)
+
+
+@pytest.mark.parametrize("W,H,spp", [(1, 1, 1), (70, 37, 1), (43, 21, 2), (33, 18, 4), (37, 9, 5), (66, 5, 8)])
+def test_pitch_of_the_nll_the_lobes_and_the_ceiling(W, H, spp):
+    """NLL and gradient, K-lobe and positional training and the ceiling on padded
+    planes: the bits of the unpadded calls, NaN (positions, hit distances,
+    parameters, records) or 255 in the padding, which stays as it is."""
+    say(f"case: padded nll, lobes, ceiling {W}x{H} spp {spp}")
+    seed = 8900 + W + spp
+    fr = wl.Sequence(W, H, seed).frame(0)
+    ref, cur, L = pg.DeviceFrame(fr), PView(fr, W, H), pg.lib()
+    p = pg.params(seed, frame=3)
+    rng = np.random.default_rng(seed)
+    one = np.stack([rng.uniform(0.2, 0.8, (H, W)), rng.uniform(0.2, 0.8, (H, W)), rng.uniform(0.01, 0.05, (H, W)),
+                    rng.uniform(-0.005, 0.005, (H, W)), rng.uniform(0.01, 0.05, (H, W)), rng.uniform(0.1, 0.4, (H, W))])
+    tail = np.stack([rng.uniform(0, 20, (H, W)), rng.integers(0, 17, (H, W))])
+    state = {K: np.concatenate([one] * K + [tail]).astype(np.float32) for K in (1, 2)}
+    theta = np.concatenate([one, tail]).astype(np.float32)
+    theta[5] = rng.uniform(-2, 2, (H, W))
+    go = rng.uniform(0.5, 2, (H, W)).astype(np.float32)
+
+    def same(a, b):
+        return np.array_equal(_valid(a, W).view(np.int32), host(b).view(np.int32)) and _pad_untouched(a, W)
+
+    # records drawn from a trained state, and the ceiling's radiance and hit distances
+    s_ref, s = pg.Samples(spp, H, W), PSamples(spp, H, W)
+    pg.sample_mis(p, ref.view, torch.as_tensor(state[1]).cuda(), s_ref)
+    g1 = padded(state[1], np.nan)
+    assert L.pg_sample_mis(C.byref(p), C.byref(cur.c), pg._gamma(g1), C.byref(s.c), pg._stream()) == pg.PG_OK
+    ceil = pg.Ceiling(fr["ceiling"])
+    pos = padded(fr["position"], np.nan)
+    hit_ref = torch.empty((spp, H, W), device="cuda")
+    hit = torch.full((spp, H, W + PAD), float("nan"), device="cuda")
+    pg.light_ceiling(ceil, ref.view, ref.position, s_ref, hit_ref)
+    ptr = lambda t: C.c_void_p(t.data_ptr())
+    assert L.pg_light_ceiling(C.byref(ceil.c), C.byref(cur.c), ptr(pos), C.byref(s.c), ptr(hit),
+                              pg._stream()) == pg.PG_OK
+    torch.cuda.synchronize()
+    for name in ("dir", "pdf_mix", "pdf_brdf", "radiance"):
+        assert same(getattr(s, name), getattr(s_ref, name)), name
+    assert same(hit, hit_ref)
+    # NLL and gradient
+    nll_ref, grad_ref = pg.nll_backward(p, ref.view, s_ref, torch.as_tensor(theta).cuda(),
+                                        grad_out=torch.as_tensor(go).cuda())
+    th, gop = padded(theta, np.nan), padded(go, np.nan)
+    nll = torch.full((H, W + PAD), float("nan"), device="cuda")
+    grad = torch.full((8, H, W + PAD), float("nan"), device="cuda")
+    assert L.pg_nll_backward(C.byref(p), C.byref(cur.c), C.byref(s.c), ptr(th), ptr(gop), ptr(grad), ptr(nll),
+                             pg._stream()) == pg.PG_OK
+    torch.cuda.synchronize()
+    assert same(nll, nll_ref) and same(grad, grad_ref)
+    # training, directional and positional
+    for K in (1, 2):
+        for vpl in (False, True):
+            g_ref, g = torch.as_tensor(state[K]).cuda(), padded(state[K], np.nan)
+            if vpl:
+                pg.em_update_vpl(p, K, ref.view, ref.position, s_ref, hit_ref, g_ref)
+                st = L.pg_em_update_vpl(C.byref(p), K, C.byref(cur.c), ptr(pos), C.byref(s.c), ptr(hit), ptr(g),
+                                        pg._stream())
+            else:
+                pg.em_update_lobes(p, K, ref.view, s_ref, g_ref)
+                st = L.pg_em_update_lobes(C.byref(p), K, C.byref(cur.c), C.byref(s.c), ptr(g), pg._stream())
+            assert st == pg.PG_OK
+            torch.cuda.synchronize()
+            assert same(g, g_ref), (K, vpl)
+            assert W * H == 1 or not np.array_equal(_valid(g, W), state[K]), (K, vpl)
