@@ -174,11 +174,12 @@ __device__ __forceinline__ int reproject_pixel(const ParamsK &P, const ViewK &cu
 // First-bounce estimate of one pixel: the mean over its samples of
 // f_r L cos / D (null samples count zero), the Monte Carlo estimator of the
 // reflected radiance with the mixture density of the samples.  Bound by HBM
-// (21 B a record, 36 B a pixel).  All of a record is loaded before any of it is
-// tested: with the strategy tested first, its other loads waited for that one
-// (1080p: 90.8 us at 8 spp, now 77.7: 5.4 TB/s; 19.7 and 19.1 at 1 spp).  The
-// records of four samples in flight cost 19 registers and, where there are not
-// as many samples, loads (1 spp 20.7, 3 spp 32.7 against 30.0, 8 spp 80.8).
+// (21 B a record, 36 B a pixel).  A record is loaded and evaluated without a
+// branch on what it holds: with its strategy tested first, its other loads
+// waited for that one (1080p: 90.8 us at 8 spp, now 78: 5.4 TB/s; 19.7 and 19.0
+// at 1 spp).  The records of four samples in flight cost 19 registers and, where
+// there are not as many samples, loads (1 spp 20.7, 3 spp 32.7 against 30.1, 8
+// spp 80.8).
 __global__ __launch_bounds__(256) void k_estimate(ParamsK P, ViewK v, SamplesK S, float *__restrict__ out) {
   int x, y;
   stream_xy(v.W, v.H, x, y);
@@ -194,17 +195,12 @@ __global__ __launch_bounds__(256) void k_estimate(ParamsK P, ViewK v, SamplesK S
     for (int s = 0; s < S.spp; ++s) {
       const int r = s * plane + idx;
       const uint32_t code = at(S.strat, r);
-      const float D = at(S.pmix, r);
-      float L = at(S.L, r);
-      V3 w = load3(S.dir, splane, r);
-      // (keeps the compiler from moving these loads behind the test)
-      asm volatile("" : "+v"(L), "+v"(w.x), "+v"(w.y), "+v"(w.z));
-      if (!(code == 1 || code == 2) || !(D > 0.0f)) continue;
-      const V3 l = to_local(px.f, normalized(w));
-      if (l.z <= 0.0f) continue;
+      const float D = at(S.pmix, r), L = at(S.L, r);
+      const V3 l = to_local(px.f, normalized(load3(S.dir, splane, r)));
       float f, pb;
       brdf_eval(px, l, f, pb);
-      acc += f * L * l.z / D;
+      const float sum = acc + f * L * l.z / D;
+      acc = (code == 1 || code == 2) && D > 0.0f && l.z > 0.0f ? sum : acc;
     }
     acc /= (float)S.spp;
   }
