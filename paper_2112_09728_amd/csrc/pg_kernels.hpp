@@ -450,10 +450,10 @@ __global__ __launch_bounds__(256) void k_pdf(ParamsK P, ViewK v, const TG *__res
 // four pixels of a row a lane in blocks of 32x8 lanes (128x8 pixels): 16-byte
 // loads and stores, and four independent chains of arithmetic to cover them.
 // Bound by HBM: 17 B a record and 1 B a pixel.  One pixel a lane and all of its
-// samples in turn took 66.0 us at 1080p and 8 spp (now 44.6: 6.4 TB/s, part of
-// it from the Infinity Cache) and 33.8 us at 4K and 1 spp (now 23.2).  Without
-// FOUR one pixel a lane (64x4), a quarter of the work in each: the shorter
-// chain where the lanes do not fill the chip anyway.
+// samples in turn took 79 us in a 1080p frame of 8 spp (now 57: 5.3 TB/s) and,
+// on records that the Infinity Cache partly holds, 66 us (now 45) and at 4K and
+// 1 spp 34 us (now 23).  Without FOUR one pixel a lane (64x4), a quarter of the
+// work in each: the shorter chain where the lanes do not fill the chip anyway.
 template <bool FOUR>
 __global__ __launch_bounds__(256) void k_light(LightsK Lt, ViewK v, const uint8_t *__restrict__ vis,
                                                SamplesK S) {
@@ -1175,7 +1175,7 @@ __device__ __forceinline__ void em_tile(const ParamsK &P, const ViewK &v, const 
 // runs over the first planes, the records area is restaged with the last
 // planes, and the same sums continue over them.  Each pass keeps the
 // training set's order, so the result does not depend on the tile shape.
-// What bounds it at 1080p and 8 spp (333 us; 381 before its records were
+// What bounds it at 1080p and 8 spp (333 to 341 us; 381 before its records were
 // staged in groups and its lists kept by address): VALU issue 59% of the
 // cycles at 2.6 of 3 waves per SIMD; without any visit 205 us, with records
 // that hit the caches 293.  Reading the second pass's records ahead into
@@ -1373,7 +1373,7 @@ __device__ __forceinline__ void em_tile2(const ParamsK &P, const ViewK &v, const
 // LDS and registers of a tile, several blocks share each CU, which hides the
 // loads of one block behind the arithmetic of the others better than a
 // persistent loop with register prefetch.
-// TWO: the two-pass tile (online EM above spp 1; em2_lds_front).
+// TWO: the two-pass tile (online EM from spp 4; em2_lds_front).
 template <typename TG, int TW, int TH, bool STALE, bool TWO = false, bool BATCH = false>
 __global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(TWO ? 5 : 8))) void k_em(ParamsK P, ViewK v, SamplesK S, TG *__restrict__ gamma,
                                                int iterations, int tiles_x, int n_tiles) {
@@ -1409,8 +1409,8 @@ struct NllCtx {
 // it: the picks of a pixel are examined once against the staged records and
 // only the kept ones visited, by lanes sorted to nearly equal lists.  (One
 // lane per pixel in image order visited all of its candidates: 24 visits a
-// wave at spp 4, where the sorted lists need about 15.)  4K, 4 spp: 709 us for
-// the loss and 781 for the gradient, VALU issue 83% of the cycles; 922 us each
+// wave at spp 4, where the sorted lists need about 15.)  4K, 4 spp: 635 us for
+// the loss, 710 for the gradient, 731 for both, bound by VALU issue; 922 us each
 // before.
 template <bool LOSS, bool GRAD>
 struct NllOp {

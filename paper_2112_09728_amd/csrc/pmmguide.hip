@@ -189,16 +189,16 @@ struct Tile {
 constexpr size_t kMaxTileLds = 64 * 1024;
 constexpr Tile kTiles[] = {{32, 8}, {16, 16}, {64, 4}, {32, 4}, {16, 8}, {64, 2}, {32, 16}, {64, 8}};
 
-// Default training tile per spp (1080p pan, EM per frame).  The two-pass
-// tile (online EM from spp 4) runs best at 16x16 up to spp 6 (spp 4 201 us
-// against 216 at 32x8, spp 5 235 against 272, spp 6 250 against 289: 16x16
-// holds one block more per CU) and at 32x8 above (spp 7 317 against 328, spp 8
-// 336 against 343: 3 blocks per CU either way).
+// Default training tile per spp (1080p, EM per frame).  The two-pass tile (from
+// spp 4) runs best at 16x16 up to spp 6 (spp 4 203 us against 220 at 32x8, spp 5
+// 240 against 275, spp 6 255 against 293: 16x16 holds one block more per CU) and
+// at 32x8 above (spp 7 323 against 330, spp 8 341 against 346: 3 blocks per CU
+// either way).
 // The single-pass tile (up to spp 3, and batch EM or the stale test above):
-// 32x8 up to spp 4 (spp 1 113 us; 16x16 111, 64x8 110, but 5% behind at 4K and
-// 4% at 640x360; spp 3 167 against 170 at 16x16); above, the staged records
-// limit how many blocks share a CU's LDS, and the shape that keeps the most
-// waves resident wins: 16x16 at spp 5 (230 us), 16x8 at spp 6-8 (spp 8 440).
+// 32x8 up to spp 4 (spp 1 111 us; 16x16 and 64x8 112, 5% behind at 4K and 4% at
+// 640x360; spp 3 170 against 173 at 16x16); above, the staged records limit how
+// many blocks share a CU's LDS, and the shape that keeps the most waves resident
+// wins: 16x16 at spp 5 (231 us), 16x8 at spp 6-8 (spp 8 443).
 Tile default_tile(int spp, bool two) {
   if (two) return spp <= 6 ? Tile{16, 16} : Tile{32, 8};
   return spp <= 4 ? Tile{32, 8} : (spp == 5 ? Tile{16, 16} : Tile{16, 8});
@@ -215,12 +215,14 @@ size_t tile_lds(Tile t, int spp, bool two) {
 
 // Whether a training launch takes the two-pass tile: online EM from spp 4
 // without the stale-history test (batch EM revisits the whole list every
-// iteration, and the test reads it before the E-step).  At 1080p EM per
-// frame, two passes against one at its best tile: spp 4 201 us against 214,
-// spp 6 252 against 312, spp 8 333 against 440 (spp 5 alone 237 against 230);
-// below, the single-pass tile already keeps 4 blocks or more per CU and the
-// second pass costs more than it gains (spp 3 190 against 168, spp 2 167
-// against 144).
+// iteration, and the test reads it before the E-step).  1080p, EM per frame, two
+// passes against one at its best tile: spp 4 203 us against 219, spp 6 255
+// against 316, spp 8 341 against 443; below, the single-pass tile already keeps 4
+// blocks or more per CU and the second pass costs more than it gains (spp 3 190
+// against 170, spp 2 165 against 141).  At spp 5 one pass is 4% ahead (231
+// against 240): it keeps two, because the order of the sums is stated for the
+// update from spp 4 on, and because a requested tile of 64x4, which fits the LDS
+// there only in two passes, would be refused.
 bool em_two_pass(int spp, int batch, uint32_t flags) { return em2_spp(spp) && !batch && !(flags & PG_STALE_RESET); }
 
 pg_status pick_tile(const pg_params *p, int spp, Tile &t, bool two = false) {
