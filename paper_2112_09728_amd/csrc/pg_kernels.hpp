@@ -200,7 +200,7 @@ __global__ __launch_bounds__(256) void k_estimate(ParamsK P, ViewK v, SamplesK S
       float f, pb;
       brdf_eval(px, l, f, pb);
       const float sum = acc + f * L * l.z / D;
-      acc = (code == 1 || code == 2) && D > 0.0f && l.z > 0.0f ? sum : acc;
+      acc = (code == 1 || code == 2) && D > 0.0f && !(l.z <= 0.0f) ? sum : acc;
     }
     acc /= (float)S.spp;
   }

@@ -106,3 +106,33 @@ def test_guided_estimator_against_brdf_sampling():
     rr, lo, hi = paired_ratio_ci(np.concatenate(pairs_g), np.concatenate(pairs_b))
     say(f"  guided / BRDF-only MSE over the evaluated frames: {rr:.3f}, paired bootstrap 95% [{lo:.3f}, {hi:.3f}]")
     assert ratio < 1.0
+
+
+@pytest.mark.parametrize("spp", [1, 3, 8])
+def test_estimate_of_records_that_are_not_finite(spp):
+    """A record that counts (a BRDF or guided draw with a density) and holds a
+    NaN direction, radiance or infinity shows in its pixel's estimate; one that
+    does not count changes nothing, whatever it holds."""
+    W, H, seed = 67, 19, 7300 + spp
+    scene = wl.make_scene(W, H, seed)
+    rng = np.random.default_rng(seed)
+    p, view = pg.params(seed, frame=5), gpu_view(scene)
+    s = pg.Samples(spp, H, W)
+    pg.sample_mis(p, view, dev(random_gamma(H, W, rng)), s)
+    pg.light_field(pg.lights_struct(scene["lights"], float(scene["ambient"])), view, dev(scene["vis"]), s)
+    clean = host(pg.estimate(p, view, s))
+    code, D = host(s.strategy), host(s.pdf_mix)
+    live = ((code == 1) | (code == 2)) & (D > 0)
+    pick = rng.random((spp, H, W)) < 0.1
+    d, L = host(s.dir).copy(), host(s.radiance).copy()
+    what = rng.integers(0, 3, (spp, H, W))
+    d[:, pick & (what == 0)] = np.nan
+    L[pick & (what == 1)] = np.nan
+    L[pick & (what == 2)] = np.inf
+    s.dir.copy_(dev(d))
+    s.radiance.copy_(dev(L))
+    got = host(pg.estimate(p, view, s))
+    bad = (pick & live).any(0)
+    assert bad.sum() > 50 and (pick & ~live).any()
+    assert not np.isfinite(got[bad]).any()
+    assert (got[~bad] == clean[~bad]).all()
