@@ -1395,7 +1395,7 @@ __global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(TWO ? 5 
 // ---------------------------------------------------------------------------
 // Weighted NLL of the mixture over the training set and its adjoint.
 struct NllAccum {
-  float loss, gmx, gmy, gxx, gxy, gyy, gl;  // loss in units of ln 2
+  float loss, gmx, gmy, gxx, gxy, gyy, gl;
 };
 
 struct NllCtx {
@@ -1466,7 +1466,7 @@ struct NllOp {
       D = far ? fmaf(c.one_m_pi * 0x1p32f, pb, gs) : D;
       off = far ? 32.0f : 0.0f;
     }
-    if (LOSS) a.loss = fmaf(w, off - __builtin_amdgcn_logf(D), a.loss);
+    if (LOSS) a.loss = fmaf(w, 0.693147180559945309417f * (off - __builtin_amdgcn_logf(D)), a.loss);
     if (GRAD) {
       // the quotient corrected by its remainder, as a division rounds it (1
       // where the Gaussian is alone)
@@ -1494,7 +1494,7 @@ struct NllOp {
       g[4] = sc * 2.0f * (a.gyy * l22);
       g[5] = sc * a.gl;
     }
-    if (LOSS) g[6] = a.loss * 0.693147180559945309417f;
+    if (LOSS) g[6] = a.loss;
   }
   static constexpr bool put(int ch) { return (GRAD && ch < 6) || (LOSS && ch == 6); }
   __device__ __forceinline__ void store(int plane, int idx, const float out[8]) const {

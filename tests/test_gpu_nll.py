@@ -250,3 +250,33 @@ def test_nll_tile_shapes_bitwise_identical(spp):
         torch.cuda.synchronize()
         assert torch.equal(nll, nll0) and torch.equal(loss_only, nll0), (tw, th_)
         assert torch.equal(grad, grad0) and torch.equal(grad_only, grad0), (tw, th_)
+
+
+def test_nll_next_to_the_largest_number():
+    """A pixel whose loss, 2.5e38 to 3.3e38, is a number in FP32 (the same record
+    everywhere, the weight scaled to reach it) keeps it: sums are formed in
+    natural logarithms, not in units that overflow before they do."""
+    say("case: nll next to FP32's largest number")
+    W, H = 45, 9
+    one = np.ones((H, W), np.float32)
+    scene = dict(normal=np.stack([0 * one, 0 * one, one]), view_dir=np.stack([0 * one, 0.6 * one, 0.8 * one]),
+                 depth=one, roughness=0.5 * one, albedo=0.5 * one)
+    w = O.sq2hemi(np.array([[0.42, 0.55]]))[0].astype(np.float32)
+    th = np.stack([0.8 * one, 0.8 * one, 0.05 * one, 0 * one, 0.05 * one, -2 * one, 0 * one, 16 * one]).astype(np.float32)
+    rec = dict(dir=np.broadcast_to(w[:, None, None, None], (3, 1, H, W)).copy(),
+               pdf_mix=np.full((1, H, W), 0.3, np.float32), pdf_brdf=np.full((1, H, W), 0.3, np.float32),
+               strategy=np.ones((1, H, W), np.uint8), radiance=np.ones((1, H, W), np.float32))
+    P, ov = O.params(7, frame=2), O.OView(scene)
+    base, _ = O.nll(P, ov, rec, th)
+    # interior pixels have the same six members (own and five picks)
+    top = base.max()
+    assert top > 0
+    rec["radiance"][:] = (3.3e38 / top * 0.999)
+    nll_o, _ = O.nll(P, ov, rec, th)
+    s = pg.Samples.wrap(*(dev(rec[k]) for k in ("dir", "pdf_mix", "pdf_brdf", "strategy", "radiance")))
+    nll, _ = pg.nll_backward(pg.params(7, frame=2), gpu_view(scene), s, dev(th), want_grad=False)
+    torch.cuda.synchronize()
+    n = host(nll)
+    big = nll_o > 2.5e38
+    assert big.sum() > 50
+    assert (np.abs(n - nll_o) <= 2e-5 * nll_o).all()
